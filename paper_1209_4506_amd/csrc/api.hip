@@ -115,6 +115,28 @@ void unit_root(long t, long n, double &c, double &s)
     }
 }
 
+// The triangular frame of a cell (ProbDesc::frame and tri): Gram-Schmidt from
+// the row c up, each residual orthogonalized twice so that the frame stays
+// orthonormal in strongly skewed cells too.
+void set_frame(ProbDesc &d)
+{
+    auto dot = [](const double *x, const double *y) { return x[0] * y[0] + x[1] * y[1] + x[2] * y[2]; };
+    for (int k = 2; k >= 0; --k) {
+        double v[3] = {d.A[3 * k], d.A[3 * k + 1], d.A[3 * k + 2]};
+        for (int pass = 0; pass < 2; ++pass)
+            for (int m = 2; m > k; --m) {
+                const double *e = d.frame + 3 * m, p = dot(v, e);
+                for (int c = 0; c < 3; ++c) v[c] -= p * e[c];
+            }
+        const double len = std::sqrt(dot(v, v));
+        for (int c = 0; c < 3; ++c) d.frame[3 * k + c] = v[c] / len;
+    }
+    const double *a = d.A, *b = d.A + 3, *c = d.A + 6;
+    for (int x = 0; x < 3; ++x) d.tri[x] = dot(a, d.frame + 3 * x) / d.dims[0];
+    for (int x = 1; x < 3; ++x) d.tri[2 + x] = dot(b, d.frame + 3 * x) / d.dims[1];
+    d.tri[5] = dot(c, d.frame + 6) / d.dims[2];
+}
+
 struct Launch {
     int plan;    // compiled radix plan (index in HARTREE_PLANS) or -1
     int p_log2;  // pencils per workgroup, log2
@@ -158,6 +180,7 @@ struct hartree_plan_s {
            o_spec2 = 0, ws_size = 0;
     int32_t cap_pa = 0;
     bool wide = false;  // some truncation window can hold two images of one grid point
+    bool many = false;  // ... or of two grid points of one brick
     unsigned char *ws = nullptr;
     // profiling: events bracketing each kernel group
     struct ProfRec {
@@ -465,6 +488,12 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
             d.hfl[k] = float(d.h[k] - double(d.hf[k]));
         }
         for (int k = 0; k < 9; ++k) d.A[k] = A[k];
+        set_frame(d);
+        for (int k = 0; k < 9; ++k) {
+            const double e = A[k] / N[k / 3];
+            d.step[k] = float(e);
+            d.stepl[k] = float(e - double(d.step[k]));
+        }
         d.separable = (ortho && A[0] > 0.0 && A[4] > 0.0 && A[8] > 0.0) ? 1 : 0;
         if (!d.separable) p->general = true;
         // pass tiles: default radix plan and pencils per workgroup per axis
@@ -511,6 +540,7 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
             const double h = 6.283185307179586476925286766559 / (bn * N[x]);
             const double w = std::floor(2.0 * p->cutoff * p->max_sigma / h) + 1.0;
             if (w + 1.0 > N[x]) p->wide = true;  // window points (+1 for rounding) exceed the axis
+            if (w + 1.0 + bsz[x] > N[x]) p->many = true;
             int64_t nbx = d.nbricks[x];  // most bricks one atom's window touches along x
             if (w < N[x]) {
                 const int64_t bnd = int64_t(std::ceil((w - 1.0) / bsz[x])) + 2;
@@ -718,6 +748,7 @@ SplatArgs splat_args(hartree_plan p, int32_t natoms, const double *pos, const do
     a.order = (p->nprob > 1 && !p->general) ? reinterpret_cast<int32_t *>(p->ws + p->o_order) : nullptr;
     a.general = p->general ? 1 : 0;
     a.wide = p->wide ? 1 : 0;
+    a.many = p->many ? 1 : 0;
     // |g|, |gd| of a c-axis factor stay below 4 max(1, max_sigma) (a few
     // images at most, |d| e^(-d^2 / 2 sigma^2) <= 0.61 sigma): scaled by
     // 2^b_exp they stay below 2^14, inside the 16-bit range

@@ -2,274 +2,781 @@
 // cells that are not diagonal; diagonal cells use the separable kernels).
 //
 // In a general cell a Gaussian is not a product of per-axis factors, so each
-// (grid point, atom) pair is evaluated directly: the point's displacement
-// from the atom's nearest image inside the atom's index window is
-//   d = u_a a' + u_b b' + u_c c' - rb,   a' = a / Na, ...,
-// with u_x the point's unwrapped offset from the window start lo_x and
-// rb = R - sum_x (lo_x / N_x) x-th cell row (formed in double, small), and
-// the contribution is w exp(-|d|^2 / (2 sigma^2)) inside the cutoff sphere
-// |d| <= cutoff sigma (the truncation of the CPU reference as well).
+// (grid point, atom image) pair is evaluated directly, inside the cutoff
+// sphere |d| <= cutoff sigma (the truncation of the CPU reference as well).
+// Most points of a listed brick lie outside the sphere (at 160^3 in the
+// diamond FCC cell 78%), so both precisions first place each atom image's
+// sphere in the problem's triangular frame (ProbDesc tri: the third axis along
+// the cell row c, the second in the plane of b and c, where the points of a
+// run of grid indices lie in a box) and pass over whole runs of points that
+// the sphere does not reach.  A wavefront takes 64 points at a time, its sums
+// (splat) in registers, a brick's grad_rho (adjoint) in LDS; it reads the
+// brick's sorted list 64 entries at a time, one entry per lane, and takes the
+// entries whose spheres reach its points one by one, broadcast from their
+// lane's registers.
 //
-// One workgroup per brick (the plan's brick size); atoms come from the same
-// sorted per-brick lists as the separable kernels, staged in LDS in chunks.
+// Bound by vector and exponential issue over the points near the spheres.
+// Diamond FCC cell, 160^3, 1,024 atoms, FP32: splat 896 -> 134 us, adjoint
+// 1,492 -> 161 us; sheared cell, 72 x 80 x 90, 108 atoms, FP64: 450 -> 48 and
+// 624 -> 78 us (before: every point of every listed brick, with the wrapped
+// index arithmetic per pair, and one pass over LDS per atom).
 #include "splat_common.hpp"
 
 namespace hartree {
 
-constexpr int kGenThreads = 256;
-constexpr int kGenChunk = 64;
-// points per brick: FP32 plans use kMI x kMJ x kMK bricks, FP64 plans kBI x kBJ x kBK
-template <typename T>
-constexpr int gen_max_points()
+// smallest |x| over [lo, hi]
+__device__ __forceinline__ double gap(double lo, double hi)
 {
-    return sizeof(T) == 4 ? kMI * kMJ * kMK : kBI * kBJ * kBK;
+    return lo > 0.0 ? lo : (hi < 0.0 ? -hi : 0.0);
 }
 
-template <typename T>
-struct StagedC {
-    T rb[3], rbl[3];  // rb and its rounding remainder (FP32 carries rb in two floats)
-    int r0[3];   // (first index of the brick - lo_x) mod N_x
-    int wl[3];   // window width per axis (0: touches nothing)
-    T inv2s2, w, rc2;
+__device__ __forceinline__ int lane_value(int x, int q) { return __builtin_amdgcn_readlane(x, q); }
+__device__ __forceinline__ float lane_value(float x, int q)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), q));
+}
+__device__ __forceinline__ double lane_value(double x, int q)
+{
+    const uint64_t b = __double_as_longlong(x);
+    const uint32_t l = __builtin_amdgcn_readlane(int(uint32_t(b)), q), h = __builtin_amdgcn_readlane(int(uint32_t(b >> 32)), q);
+    return __longlong_as_double(int64_t((uint64_t(h) << 32) | l));
+}
+
+// x plus its value moved across lanes by a data-parallel move (lanes without
+// a source, or outside the row mask, add zero)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_plus(float x)
+{
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_plus(double x)
+{
+    const uint64_t b = __double_as_longlong(x);
+    const uint32_t l = __builtin_amdgcn_update_dpp(0, int(uint32_t(b)), CTRL, ROWS, 0xf, false);
+    const uint32_t h = __builtin_amdgcn_update_dpp(0, int(uint32_t(b >> 32)), CTRL, ROWS, 0xf, false);
+    return x + __longlong_as_double(int64_t((uint64_t(h) << 32) | l));
+}
+
+// An atom's periodic images over one brick.  Unwrapped indices are counted from
+// the atom's window start lo: the brick's first point g0 lies at u = g0 - lo +
+// m N for image m (per axis), and the images whose points meet the window are
+// numbered 0 .. count - 1, axis a slowest, from u0 on.  r: the atom relative to
+// the window start, in the triangular frame (formed from the small Cartesian
+// difference rb, which keeps the projection's rounding below that of rb).
+struct GenImages {
+    double r[3];
+    int u0[3], mc[3];
+    int count;
 };
 
-template <typename T>
-__device__ __forceinline__ void stage_general(StagedC<T> *dst, const SplatArgs &a, const ProbDesc &d,
-                                              const int bidx[3], int64_t off, int c0, int nc, int t)
+__device__ __forceinline__ GenImages gen_images(const AtomInfo &in, const ProbDesc &d, const int g0[3], double rb[3])
 {
-    if (t >= nc) return;
-    const int atom = a.list_sorted[off + c0 + t];
-    const AtomInfo in = a.info[atom];
-    StagedC<T> s;
-    double rb[3] = {in.X[0], in.X[1], in.X[2]};
+    GenImages im;
+    im.count = 1;
+    for (int c = 0; c < 3; ++c) rb[c] = in.X[c];
     for (int x = 0; x < 3; ++x) {
         const double f = double(in.lo[x]) / d.dims[x];
         for (int c = 0; c < 3; ++c) rb[c] -= f * d.A[3 * x + c];
-        s.r0[x] = wrapi(bidx[x] * d.bsz[x] - in.lo[x], d.dims[x]);
-        s.wl[x] = in.hi[x] >= in.lo[x] ? in.hi[x] - in.lo[x] + 1 : 0;
+        // u in [1 - bsz, hi - lo], in steps of N
+        const int n = d.dims[x], first = 1 - d.bsz[x];
+        im.u0[x] = first + wrapi(g0[x] - in.lo[x] - first, n);
+        im.mc[x] = im.u0[x] <= in.hi[x] - in.lo[x] ? (in.hi[x] - in.lo[x] - im.u0[x]) / n + 1 : 0;
+        im.count *= im.mc[x];
     }
-    for (int c = 0; c < 3; ++c) {
-        s.rb[c] = T(rb[c]);
-        s.rbl[c] = T(rb[c] - double(s.rb[c]));
-    }
-    s.inv2s2 = T(in.inv2s2);
-    s.w = T(in.w);
-    const double rc = a.cutoff * sqrt(0.5 / in.inv2s2);
-    s.rc2 = T(rc * rc);
-    dst[t] = s;
+    for (int x = 0; x < 3; ++x) im.r[x] = rb[0] * d.frame[3 * x] + rb[1] * d.frame[3 * x + 1] + rb[2] * d.frame[3 * x + 2];
+    return im;
 }
 
-// Sum over the images of one atom inside its window of f(e, d) for the point
-// at local offsets l = (li, lj, lk) of the brick (g = global index < N).
-// e3 / e3l: the grid steps a / Na, b / Nb, c / Nc and their rounding
-// remainders; each displacement component is formed with one rounding of
-// the large terms (fma chain) plus the small remainder terms
-template <typename T, typename F>
-__device__ __forceinline__ void for_images(const StagedC<T> &at, const int l[3], const int n[3], const T e3[9],
-                                           const T e3l[9], F f)
+__device__ __forceinline__ GenImages no_images()
 {
-    int u0[3];
+    GenImages im;
     for (int x = 0; x < 3; ++x) {
-        int u = at.r0[x] + l[x];
-        if (u >= n[x]) u -= n[x];
-        u0[x] = u;
+        im.r[x] = 0.0;
+        im.u0[x] = 0;
+        im.mc[x] = 1;
     }
-    for (int ua = u0[0]; ua < at.wl[0]; ua += n[0])
-        for (int ub = u0[1]; ub < at.wl[1]; ub += n[1])
-            for (int uc = u0[2]; uc < at.wl[2]; uc += n[2]) {
-                T dv[3];
-                for (int c = 0; c < 3; ++c)
-                    dv[c] = fma(T(ua), e3[c], fma(T(ub), e3[3 + c], fma(T(uc), e3[6 + c], -at.rb[c]))) +
-                            (T(ua) * e3l[c] + T(ub) * e3l[3 + c] + T(uc) * e3l[6 + c] - at.rbl[c]);
-                const T d2 = dv[0] * dv[0] + dv[1] * dv[1] + dv[2] * dv[2];
-                if (d2 <= at.rc2) f(expT<T>(-d2 * at.inv2s2), dv);
-            }
+    im.count = 0;
+    return im;
 }
 
-struct BrickGeom {
-    int bidx[3], bsz[3], n[3], npts;
+// image i of an atom: the offset u of the brick's first point from the window
+// start, and its displacement p in the triangular frame
+struct GenShift {
+    int u[3];
+    double p[3];
 };
-
-__device__ __forceinline__ BrickGeom brick_geom(const ProbDesc &d, int64_t b)
+__device__ __forceinline__ GenShift gen_shift(const GenImages &im, const ProbDesc &d, int i)
 {
-    BrickGeom g;
-    const int lb = int(b - d.brick_off);  // bricks of one problem fit 32 bits
-    g.bidx[2] = lb % d.nbricks[2];
-    g.bidx[1] = (lb / d.nbricks[2]) % d.nbricks[1];
-    g.bidx[0] = lb / (d.nbricks[2] * d.nbricks[1]);
-    for (int x = 0; x < 3; ++x) {
-        g.bsz[x] = d.bsz[x];
-        g.n[x] = d.dims[x];
+    GenShift s;
+    for (int x = 0; x < 3; ++x) s.u[x] = im.u0[x];
+    if (i > 0) {
+        const int uv = i / im.mc[2], u = uv / im.mc[1];
+        s.u[2] += (i - uv * im.mc[2]) * d.dims[2];
+        s.u[1] += (uv - u * im.mc[1]) * d.dims[1];
+        s.u[0] += u * d.dims[0];
     }
-    g.npts = g.bsz[0] * g.bsz[1] * g.bsz[2];
+    const double ga = s.u[0], gb = s.u[1], gc = s.u[2];
+    s.p[0] = ga * d.tri[0] - im.r[0];
+    s.p[1] = ga * d.tri[1] + gb * d.tri[3] - im.r[1];
+    s.p[2] = ga * d.tri[2] + gb * d.tri[4] + gc * d.tri[5] - im.r[2];
+    return s;
+}
+
+// squared distance from the atom to the box (in the triangular frame) that
+// holds the points at offsets o .. o + e (inclusive, per axis) from the
+// brick's first point
+__device__ __forceinline__ double box_distance2(const ProbDesc &d, const double p[3], const int o[3], double ea, double eb,
+                                                double ec)
+{
+    const double *t = d.tri;
+    const double oa = o[0], ob = o[1], oc = o[2];
+    const double b1 = p[0] + oa * t[0], b2 = p[1] + oa * t[1] + ob * t[3], b3 = p[2] + oa * t[2] + ob * t[4] + oc * t[5];
+    const double g1 = gap(b1, b1 + ea * t[0]);
+    const double g2 = gap(b2 + fmin(ea * t[1], 0.0), b2 + fmax(ea * t[1], 0.0) + eb * t[3]);
+    const double g3 = gap(b3 + fmin(ea * t[2], 0.0) + fmin(eb * t[4], 0.0),
+                          b3 + fmax(ea * t[2], 0.0) + fmax(eb * t[4], 0.0) + ec * t[5]);
+    return g1 * g1 + g2 * g2 + g3 * g3;
+}
+// margin of the box tests over the rounding of box_distance2 and of rc^2
+constexpr double kBoxMargin = 1.0001;
+
+// ---------------------------------------------------------------- FP32
+// Every point is evaluated in Cartesian components, each formed with one
+// rounding of the large terms (an fma chain) plus the small remainder terms,
+// in this fixed order of operations, which the FP32 results' bits depend on:
+//   d_c = fma(ua, a_c, fma(ub, b_c, fma(uc, c_c, -rb_c)))
+//         + (fma(uc, cl_c, fma(ub, bl_c, ua al_c)) - rbl_c)
+// with u_x the point's unwrapped offset from the window start lo_x, a_c, al_c
+// ... the grid steps and their rounding remainders, and rb = R - sum_x (lo_x /
+// N_x) x-th cell row (formed in double, small) carried as rb + rbl.
+// A wavefront's 64 points are 8 (j) x 8 (k) at one i: the terms of ub and uc
+// are formed once per atom, and the sphere of 6 sigma fills 64% of the 64
+// points it reaches on average (45% of 2 x 32, 22% of whole bricks).
+
+// The grid steps and their remainders, held in vector registers: left to
+// itself the compiler reads them from the descriptor again for every point
+// and waits for the scalar loads (adjoint 194 us instead of 161 at 160^3).
+struct GenSteps {
+    float e[9], l[9];
+};
+__device__ __forceinline__ GenSteps gen_steps(const ProbDesc &d)
+{
+    GenSteps g;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        g.e[k] = d.step[k];
+        g.l[k] = d.stepl[k];
+        asm volatile("" : "+v"(g.e[k]), "+v"(g.l[k]));
+    }
     return g;
 }
 
-// local offsets of brick point p (c fastest)
-__device__ __forceinline__ void brick_point(const BrickGeom &g, int p, int l[3])
+// one list entry per lane
+struct GenAtom32 {
+    GenImages im;
+    float rb[3], rbl[3], inv2s2, w, rc2;
+};
+__device__ __forceinline__ GenAtom32 gen_atom32(const SplatArgs &a, const ProbDesc &d, const int g0[3], int64_t e, bool use)
 {
-    l[2] = p % g.bsz[2];
-    l[1] = (p / g.bsz[2]) % g.bsz[1];
-    l[0] = p / (g.bsz[2] * g.bsz[1]);
+    GenAtom32 g;
+    g.im = no_images();
+    for (int x = 0; x < 3; ++x) g.rb[x] = g.rbl[x] = 0.0f;
+    g.inv2s2 = g.w = g.rc2 = 0.0f;
+    if (!use) return g;
+    const AtomInfo in = a.info[a.list_sorted[e]];
+    double rb[3];
+    g.im = gen_images(in, d, g0, rb);
+    for (int c = 0; c < 3; ++c) {
+        g.rb[c] = float(rb[c]);
+        g.rbl[c] = float(rb[c] - double(g.rb[c]));
+    }
+    g.inv2s2 = float(in.inv2s2);
+    g.w = float(in.w);
+    const double rc = a.cutoff * sqrt(0.5 / in.inv2s2);
+    g.rc2 = float(rc * rc);
+    return g;
 }
 
-// point p of the brick lies inside the grid
-__device__ __forceinline__ bool point_in_grid(const BrickGeom &g, const int l[3])
+// the entry of lane q in every lane
+__device__ __forceinline__ GenAtom32 lane_atom(const GenAtom32 &g, int q)
 {
-    return g.bidx[0] * g.bsz[0] + l[0] < g.n[0] && g.bidx[1] * g.bsz[1] + l[1] < g.n[1] &&
-           g.bidx[2] * g.bsz[2] + l[2] < g.n[2];
+    GenAtom32 o;
+    for (int x = 0; x < 3; ++x) {
+        o.im.r[x] = lane_value(g.im.r[x], q);
+        o.im.u0[x] = lane_value(g.im.u0[x], q);
+        o.im.mc[x] = lane_value(g.im.mc[x], q);
+        o.rb[x] = lane_value(g.rb[x], q);
+        o.rbl[x] = lane_value(g.rbl[x], q);
+    }
+    o.im.count = lane_value(g.im.count, q);
+    o.inv2s2 = lane_value(g.inv2s2, q);
+    o.w = lane_value(g.w, q);
+    o.rc2 = lane_value(g.rc2, q);
+    return o;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kGenThreads) void k_splat_general(SplatArgs a)
+// The images of the lane's entry that reach the box of points o .. o + e: bit
+// i for image i < 32; with more images all of them (bit 31 stands for the
+// images from 31 on).
+__device__ __forceinline__ uint32_t gen_hits(const GenAtom32 &g, const ProbDesc &d, const int o[3],
+                                             double ea, double eb, double ec)
 {
-    __shared__ StagedC<T> atoms[kGenChunk];
-    __shared__ T acc[gen_max_points<T>()];  // the brick's running sums
-    const int64_t b = blockIdx.x;
-    const int prob = brick_prob(a, b);
-    const ProbDesc &d = a.desc[prob];
-    const BrickGeom g = brick_geom(d, b);
-    T e3[9], e3l[9];
+    uint32_t hits = 0;
+    for (int i = 0; __any(i < g.im.count && i < 32); ++i) {
+        if (i >= g.im.count) continue;
+        const GenShift s = gen_shift(g.im, d, i);
+        if (box_distance2(d, s.p, o, ea, eb, ec) <= kBoxMargin * double(g.rc2)) hits |= 1u << i;
+    }
+    return g.im.count > 32 ? 0xffffffffu : hits;
+}
+
+// displacement terms of ub and uc of one lane's column (see above)
+struct GenColumn {
+    float h[3], ub, uc;
+};
+__device__ __forceinline__ GenColumn gen_column(const GenSteps &st, const GenAtom32 &at, int ub, int uc)
+{
+    GenColumn c;
+    c.ub = float(ub);
+    c.uc = float(uc);
+#pragma unroll
     for (int x = 0; x < 3; ++x)
-        for (int c = 0; c < 3; ++c) {
-            const double e = d.A[3 * x + c] / d.dims[x];
-            e3[3 * x + c] = T(e);
-            e3l[3 * x + c] = T(e - double(e3[3 * x + c]));
-        }
-    const int t = threadIdx.x;
-    const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
-    for (int p = t; p < g.npts; p += kGenThreads) acc[p] = T(0);
-    for (int c0 = 0; c0 < cnt; c0 += kGenChunk) {
-        const int nc = (cnt - c0) < kGenChunk ? (cnt - c0) : kGenChunk;
-        stage_general<T>(atoms, a, d, g.bidx, off, c0, nc, t);
-        __syncthreads();
-#pragma unroll 1
-        for (int p = t; p < g.npts; p += kGenThreads) {
-            int l[3];
-            brick_point(g, p, l);
-            if (!point_in_grid(g, l)) continue;
-            T s = acc[p];
-#pragma unroll 1
-            for (int q = 0; q < nc; ++q) {
-                const StagedC<T> &at = atoms[q];
-                for_images<T>(at, l, g.n, e3, e3l, [&](T e, const T *) { s += at.w * e; });
-            }
-            acc[p] = s;
-        }
-        __syncthreads();
-    }
-    const T bg = a.subtract_background ? T(a.qsum[prob] / (d.dv * double(d.npts))) : T(0);
-    T *out = reinterpret_cast<T *>(a.rho) + d.grid_off;
-    for (int p = t; p < g.npts; p += kGenThreads) {
-        int l[3];
-        brick_point(g, p, l);
-        if (!point_in_grid(g, l)) continue;
-        const int i = g.bidx[0] * g.bsz[0] + l[0], j = g.bidx[1] * g.bsz[1] + l[1], k = g.bidx[2] * g.bsz[2] + l[2];
-        out[(int64_t(i) * g.n[1] + j) * g.n[2] + k] = acc[p] - bg;
-    }
+        c.h[x] = __builtin_fmaf(c.ub, st.e[3 + x], __builtin_fmaf(c.uc, st.e[6 + x], -at.rb[x]));
+    return c;
 }
-
-template <typename T>
-__device__ __forceinline__ T wave_sum_g(T v)
+// displacement at ua; returns |d|^2
+__device__ __forceinline__ float gen_point(const GenSteps &st, const GenAtom32 &at, const GenColumn &c, float ua, float dv[3])
 {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int x = 0; x < 3; ++x) {
+        const float lo = __builtin_fmaf(c.uc, st.l[6 + x], __builtin_fmaf(c.ub, st.l[3 + x], ua * st.l[x])) - at.rbl[x];
+        dv[x] = __builtin_fmaf(ua, st.e[x], c.h[x]) + lo;
+    }
+    return __builtin_fmaf(dv[2], dv[2], __builtin_fmaf(dv[0], dv[0], dv[1] * dv[1]));
 }
 
-// adjoint: per (brick, slot) the partial sum over the brick's points of
-// grad_rho exp(-|d|^2 / (2 sigma^2)) d (the caller scales by w / sigma^2)
-template <typename T>
-__global__ __launch_bounds__(kGenThreads) void k_adjoint_general(SplatArgs a)
+// NS: planes i per wavefront
+template <int NS>
+__global__ __launch_bounds__(256) void k_splat_general32(SplatArgs a)
 {
-    __shared__ StagedC<T> atoms[kGenChunk];
-    __shared__ T gr[gen_max_points<T>()];  // the brick's grad_rho (zero outside the grid)
-    __shared__ T red[kGenThreads / 64][kGenChunk][3];
-    const int64_t b = blockIdx.x;
+    constexpr int UI = kMI / NS, UNITS = UI * (kMJ / 8) * (kMK / 8);
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int item = xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
+    const int64_t b = item / UNITS;
+    const int unit = item % UNITS;
     const int prob = brick_prob(a, b);
     const ProbDesc &d = a.desc[prob];
-    const BrickGeom g = brick_geom(d, b);
-    T e3[9], e3l[9];
-    for (int x = 0; x < 3; ++x)
-        for (int c = 0; c < 3; ++c) {
-            const double e = d.A[3 * x + c] / d.dims[x];
-            e3[3 * x + c] = T(e);
-            e3l[3 * x + c] = T(e - double(e3[3 * x + c]));
-        }
-    const int t = threadIdx.x, wave = t >> 6;
+    const BrickPos p = brick_pos(d, b);
+    const int g0[3] = {p.b0 * kMI, p.b1 * kMJ, p.b2 * kMK};
+    const int o[3] = {NS * (unit % UI), 8 * ((unit / UI) % (kMJ / 8)), 8 * (unit / (UI * (kMJ / 8)))};
+    if (g0[0] + o[0] >= d.dims[0] || g0[1] + o[1] >= d.dims[1] || g0[2] + o[2] >= d.dims[2]) return;
+    const int lj = lane >> 3, lk = lane & 7;
+    const GenSteps st = gen_steps(d);
     const int64_t off = a.offsets[b];
     const int cnt = int(a.offsets[b + 1] - off);
-    if (cnt == 0) return;
-    const T *src = reinterpret_cast<const T *>(a.grad_rho) + d.grid_off;
-    for (int p = t; p < g.npts; p += kGenThreads) {
-        int l[3];
-        brick_point(g, p, l);
-        T v = T(0);
-        if (point_in_grid(g, l)) {
-            const int i = g.bidx[0] * g.bsz[0] + l[0], j = g.bidx[1] * g.bsz[1] + l[1],
-                      k = g.bidx[2] * g.bsz[2] + l[2];
-            v = src[(int64_t(i) * g.n[1] + j) * g.n[2] + k];
+    float acc[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) acc[i] = 0.0f;
+    for (int c0 = 0; c0 < cnt; c0 += 64) {
+        const GenAtom32 mine = gen_atom32(a, d, g0, off + c0 + lane, c0 + lane < cnt);
+        const uint32_t hits = gen_hits(mine, d, o, NS - 1, 7.0, 7.0);
+        uint64_t todo = __ballot(hits != 0u);
+        while (todo) {
+            const int q = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            const uint32_t hq = lane_value(int(hits), q);
+            const GenAtom32 at = lane_atom(mine, q);
+            for (int im = 0; im < at.im.count; ++im) {
+                if (!((hq >> (im < 31 ? im : 31)) & 1u)) continue;
+                const GenShift s = gen_shift(at.im, d, im);
+                // planes the sphere reaches: lane l tests plane l
+                const int ol[3] = {o[0] + (lane & (NS - 1)), o[1], o[2]};
+                const uint32_t mask =
+                    uint32_t(__ballot(box_distance2(d, s.p, ol, 0.0, 7.0, 7.0) <= kBoxMargin * double(at.rc2)));
+                const int u0 = s.u[0] + o[0];
+                const GenColumn col = gen_column(st, at, s.u[1] + o[1] + lj, s.u[2] + o[2] + lk);
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    if (!((mask >> i) & 1u)) continue;
+                    float dv[3];
+                    const float d2 = gen_point(st, at, col, float(u0 + i), dv);
+                    const float e = expf(-d2 * at.inv2s2);
+                    const float next = __builtin_fmaf(at.w, e, acc[i]);
+                    acc[i] = d2 <= at.rc2 ? next : acc[i];
+                }
+            }
         }
-        gr[p] = v;
     }
-    for (int c0 = 0; c0 < cnt; c0 += kGenChunk) {
-        const int nc = (cnt - c0) < kGenChunk ? (cnt - c0) : kGenChunk;
-        stage_general<T>(atoms, a, d, g.bidx, off, c0, nc, t);
-        __syncthreads();
-#pragma unroll 1
-        for (int q = 0; q < nc; ++q) {
-            const StagedC<T> &at = atoms[q];
-            T f0 = T(0), f1 = T(0), f2 = T(0);
-#pragma unroll 1
-            for (int p = t; p < g.npts; p += kGenThreads) {
-                int l[3];
-                brick_point(g, p, l);
-                if (!point_in_grid(g, l)) continue;
-                const T gv = gr[p];
-                for_images<T>(at, l, g.n, e3, e3l, [&](T e, const T *dv) {
-                    const T s = gv * e;
-                    f0 += s * dv[0];
-                    f1 += s * dv[1];
-                    f2 += s * dv[2];
-                });
+    const int j = g0[1] + o[1] + lj, k = g0[2] + o[2] + lk;
+    if (j >= d.dims[1] || k >= d.dims[2]) return;
+    const float bg = a.subtract_background ? float(a.qsum[prob] / (d.dv * double(d.npts))) : 0.0f;
+    float *out = reinterpret_cast<float *>(a.rho) + d.grid_off;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int ia = g0[0] + o[0] + i;
+        if (ia < d.dims[0]) out[(int64_t(ia) * d.dims[1] + j) * d.dims[2] + k] = acc[i] - bg;
+    }
+}
+
+// below this many bricks (with one wavefront per 8 x 8 columns, fewer than
+// two per SIMD) each brick's work is cut into more, smaller pieces
+constexpr int kFewBricks = 256;
+
+// Adjoint: per list slot the partial sum over the brick's points of grad_rho
+// exp(-|d|^2 / (2 sigma^2)) d (the caller scales by w / sigma^2).  grad_rho of
+// the brick lies in LDS; each wavefront takes list entries of its own (the
+// `split` workgroups of a brick and their four wavefronts in turn) and walks
+// the whole brick for one, so that nothing waits between entries: a wavefront
+// per 8 points of k with the partial sums combined over LDS every 16 entries
+// measured 225 us at 160^3 (193 us every 8), the vector issue being 143 us.
+// The sum over a brick's points keeps one order (the bits of the forces
+// depend on it): per lane (j0, k mod 8) and kb = k / 8 over i with j0 before
+// j0 + 8, then over j0 and j0 ^ 1, over k ^ 16, 8, 4, 2, 1, and over the four
+// pairs of j0 in double.
+// MANY: several images of one atom may reach one run of points (known on the
+// host from the cell and the cutoff).
+template <bool MANY>
+__global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int split)
+{
+    __shared__ float gr[4][2 * kMI][64];  // [kb][2 i + j / 8][lane (j0, k mod 8)]
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int64_t b = blockIdx.x / split;
+    const int share = blockIdx.x - int(b) * split;
+    const int prob = brick_prob(a, b);
+    const ProbDesc &d = a.desc[prob];
+    const int64_t off = a.offsets[b];
+    const int cnt = int(a.offsets[b + 1] - off);
+    const int ways = 4 * split, way = 4 * share + wave;  // entries way, way + ways, ... are this wavefront's
+    if (4 * share >= cnt) return;
+    const BrickPos p = brick_pos(d, b);
+    const int g0[3] = {p.b0 * kMI, p.b1 * kMJ, p.b2 * kMK};
+    const int lj = lane >> 3, lk = lane & 7;
+    {
+        // zero outside the grid
+        const float *src = reinterpret_cast<const float *>(a.grad_rho) + d.grid_off;
+        const int k = g0[2] + 8 * wave + lk;
+#pragma unroll
+        for (int i = 0; i < kMI; ++i)
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb) {
+                const int ia = g0[0] + i, j = g0[1] + 8 * jb + lj;
+                const bool in = ia < d.dims[0] && j < d.dims[1] && k < d.dims[2];
+                gr[wave][2 * i + jb][lane] = *(in ? src + (int64_t(ia) * d.dims[1] + j) * d.dims[2] + k : a.zeros);
             }
-            f0 = wave_sum_g(f0);
-            f1 = wave_sum_g(f1);
-            f2 = wave_sum_g(f2);
-            if ((t & 63) == 0) {
-                red[wave][q][0] = f0;
-                red[wave][q][1] = f1;
-                red[wave][q][2] = f2;
+    }
+    __syncthreads();
+    const GenSteps st = gen_steps(d);
+    const int whole[3] = {0, 0, 0};
+    for (int c0 = 0; c0 < cnt; c0 += 64 * ways) {
+        const int mye = c0 + lane * ways + way;
+        const GenAtom32 mine = gen_atom32(a, d, g0, off + mye, mye < cnt);
+        const uint32_t hits = gen_hits(mine, d, whole, kMI - 1, kMJ - 1, kMK - 1);
+        for (int q = 0; q < 64 && c0 + q * ways + way < cnt; ++q) {
+            const uint32_t hq = lane_value(int(hits), q);
+            double v[3] = {0.0, 0.0, 0.0};
+            if (hq) {
+                const GenAtom32 at = lane_atom(mine, q);
+                const double reach = kBoxMargin * double(at.rc2);
+                // runs of points the sphere of an image reaches, 32 per kb
+                // (bit 2 i + j / 8), two kb at a time: lane l tests run l
+                auto runs = [&](const GenShift &s, int kb) {
+                    const int ol[3] = {(lane & 31) >> 1, 8 * (lane & 1), 8 * (kb + (lane >> 5))};
+                    return uint64_t(__ballot(box_distance2(d, s.p, ol, 0.0, 7.0, 7.0) <= reach));
+                };
+                auto column = [&](const GenShift &s, int kb, int jb) {
+                    return gen_column(st, at, s.u[1] + 8 * jb + lj, s.u[2] + 8 * kb + lk);
+                };
+                auto point = [&](const GenColumn &col, float ua, float g, float (&f)[3]) {
+                    float dv[3];
+                    const float d2 = gen_point(st, at, col, ua, dv);
+                    const float e = expf(-d2 * at.inv2s2);
+                    // (selected after the product: a non-finite grad_rho
+                    // beyond the sphere does not reach the atom)
+                    const float t = d2 <= at.rc2 ? g * e : 0.0f;
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) f[x] = __builtin_fmaf(dv[x], t, f[x]);
+                };
+                float z[3] = {0.0f, 0.0f, 0.0f}, y[3];
+                const bool one = !MANY || ((hq & (hq - 1)) == 0u && at.im.count <= 32);
+                const GenShift s1 = gen_shift(at.im, d, one ? __builtin_ctz(hq) : 0);
+                const uint64_t m01 = one ? runs(s1, 0) : 0, m23 = one ? runs(s1, 2) : 0;
+#pragma unroll 1
+                for (int turn = 0; turn < 4; ++turn) {
+                    const int kb = ((turn & 1) << 1) | (turn >> 1);  // 0, 2, 1, 3
+                    float f[3] = {0.0f, 0.0f, 0.0f};
+                    if (one) {
+                        uint32_t m = uint32_t((kb & 2 ? m23 : m01) >> (32 * (kb & 1)));
+                        const int u0 = s1.u[0];
+                        const GenColumn col0 = column(s1, kb, 0), col1 = column(s1, kb, 1);
+                        while (m) {
+                            const int i = __builtin_ctz(m) >> 1;
+                            const uint32_t two = m >> (2 * i);
+                            m &= ~(3u << (2 * i));
+                            const float ua = float(u0 + i);
+                            const float ga = gr[kb][2 * i][lane], gb = gr[kb][2 * i + 1][lane];
+                            if (two & 1u) point(col0, ua, ga, f);
+                            if (two & 2u) point(col1, ua, gb, f);
+                        }
+                    } else {
+                        // several images reach the brick: point by point, the
+                        // images in order
+#pragma unroll 1
+                        for (int i = 0; i < 2 * kMI; ++i) {
+                            const float g = gr[kb][i][lane];
+#pragma unroll 1
+                            for (int im = 0; im < at.im.count; ++im) {
+                                if (!((hq >> (im < 31 ? im : 31)) & 1u)) continue;
+                                const GenShift s = gen_shift(at.im, d, im);
+                                const int oi[3] = {i >> 1, 8 * (i & 1), 8 * kb};
+                                if (!(box_distance2(d, s.p, oi, 0.0, 7.0, 7.0) <= reach)) continue;
+                                point(column(s, kb, i & 1), float(s.u[0] + (i >> 1)), g, f);
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) {
+                        // j0 and j0 ^ 1 (a rotation by 8 within rows of 16 lanes)
+                        const float w = dpp_plus<0x128, 0xf>(f[x]);
+                        if (turn == 0) z[x] = w;
+                        else if (turn == 1) z[x] += w;
+                        else if (turn == 2) y[x] = w;
+                        else z[x] += y[x] + w;
+                    }
+                }
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    // k ^ 4, 2, 1 into k = 0 (shifts within rows of 16 lanes)
+                    float w = dpp_plus<0x104, 0xf>(z[x]);
+                    w = dpp_plus<0x102, 0xf>(w);
+                    w = dpp_plus<0x101, 0xf>(w);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[x] += double(lane_value(w, 16 * r));
+                }
+            }
+            const int64_t slot = off + c0 + q * ways + way;
+            if (lane < 3 && slot < a.capacity) a.bpart[slot * 3 + lane] = lane == 0 ? v[0] : (lane == 1 ? v[1] : v[2]);
+        }
+    }
+}
+
+// ---------------------------------------------------------------- FP64
+// Lane (i, j) holds the rows along c of a kBI x kBJ brick, kRun consecutive
+// points of each at a time.  In the triangular frame such a row has fixed d1
+// and d2: with s = (d1^2 + d2^2) / (2 sigma^2) and t = d3 / (sqrt(2) sigma) a
+// point's exponent is s + t^2, and t advances by a constant c along the row.
+// Both kernels deal a brick's list out to several wavefronts (four per run of
+// points in the splat, summed over LDS at the end; four or eight per brick in
+// the adjoint): with one wavefront per run of points 270 bricks left most
+// SIMDs a single wavefront, and some two (68 and 100 us in the sheared cell).
+static_assert(kBI == 8 && kBJ == 8, "a wavefront's rows");
+constexpr int kRun = 8;
+constexpr int kSeg = kBK / kRun;  // runs per row
+constexpr int kWays = 4;          // wavefronts per workgroup
+
+struct GenRows {
+    int g0[3];        // the brick's first point
+    double r[3];      // (d1, d2, d3) of the lane's row start minus the brick's first point
+    bool inside;      // the row lies inside the grid
+    int64_t row;      // its first point in the grid
+};
+
+__device__ __forceinline__ GenRows gen_rows(const ProbDesc &d, const BrickPos &p, int lane)
+{
+    GenRows r;
+    r.g0[0] = p.b0 * kBI;
+    r.g0[1] = p.b1 * kBJ;
+    r.g0[2] = p.b2 * kBK;
+    const int li = lane >> 3, lj = lane & 7;
+    r.r[0] = li * d.tri[0];
+    r.r[1] = li * d.tri[1] + lj * d.tri[3];
+    r.r[2] = li * d.tri[2] + lj * d.tri[4];
+    r.inside = r.g0[0] + li < d.dims[0] && r.g0[1] + lj < d.dims[1];
+    r.row = (int64_t(r.g0[0] + li) * d.dims[1] + r.g0[1] + lj) * d.dims[2] + r.g0[2];
+    return r;
+}
+
+// The run's eight exponentials, t_k = tm + k c for k = -4 .. 3: with x =
+// exp(-2 tm c), exp(-(s + t_k^2)) = exp(-(s + tm^2)) x^k exp(-c^2 k^2), three
+// exponentials and a few products instead of eight exponentials.  The error is
+// that of the exponents' terms, eps (s + tm^2 + |2 tm c k| + c^2 k^2), a few
+// ulps while 4 c is about a width or less; taken only for c <= 0.5 (grid
+// spacing up to 0.7 sigma), otherwise the points are evaluated one by one
+// (direct), which also keeps every factor in range.
+struct GenRun {
+    double c, k1, k2, k3, k4;  // step of t; exp(-c^2 k^2)
+    bool direct;
+};
+__device__ __forceinline__ GenRun gen_run(double c, double qc)
+{
+    GenRun r;
+    r.c = c;
+    const double reach = sqrt(qc) + 4.0 * c;  // largest |tm| of a run inside the sphere
+    r.direct = !(c <= 0.5 && qc + reach * reach < 600.0 && 8.0 * reach * c < 600.0);
+    r.k1 = exp(-c * c);
+    r.k2 = exp(-4.0 * c * c);
+    r.k3 = exp(-9.0 * c * c);
+    r.k4 = exp(-16.0 * c * c);
+    return r;
+}
+__device__ __forceinline__ GenRun lane_run(const GenRun &r, int q)
+{
+    GenRun o;
+    o.c = lane_value(r.c, q);
+    o.k1 = lane_value(r.k1, q);
+    o.k2 = lane_value(r.k2, q);
+    o.k3 = lane_value(r.k3, q);
+    o.k4 = lane_value(r.k4, q);
+    o.direct = lane_value(r.direct ? 1 : 0, q) != 0;
+    return o;
+}
+// in[k + 4]: point k lies inside the sphere; e is meaningful only there
+__device__ __forceinline__ void gen_exps(const GenRun &r, double s, double tm, double qc, double (&t)[kRun], bool (&in)[kRun],
+                                         double (&e)[kRun])
+{
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) {
+        t[j] = fma(double(j - 4), r.c, tm);
+        in[j] = fma(t[j], t[j], s) <= qc;
+    }
+    if (r.direct) {
+#pragma unroll
+        for (int j = 0; j < kRun; ++j) e[j] = exp(-fma(t[j], t[j], s));
+        return;
+    }
+    const double A = exp(-fma(tm, tm, s));
+    const double x = exp(-2.0 * tm * r.c), y = exp(2.0 * tm * r.c);
+    const double x2 = x * x, y2 = y * y;
+    const double A1 = A * r.k1, A2 = A * r.k2, A3 = A * r.k3;
+    e[0] = (A * r.k4) * (y2 * y2);
+    e[1] = A3 * (y2 * y);
+    e[2] = A2 * y2;
+    e[3] = A1 * y;
+    e[4] = A;
+    e[5] = A1 * x;
+    e[6] = A2 * x2;
+    e[7] = A3 * (x2 * x);
+}
+
+// One list entry per lane: its images, sc = 1 / (sqrt(2) sigma), the weight
+// and the constants of its runs.
+struct GenAtom64 {
+    GenImages im;
+    double sc, w;
+    GenRun run;
+};
+__device__ __forceinline__ GenAtom64 gen_atom64(const SplatArgs &a, const ProbDesc &d, const int g0[3], int64_t e, bool use,
+                                                double qc)
+{
+    GenAtom64 g;
+    g.im = no_images();
+    g.sc = 1.0;
+    g.w = 0.0;
+    if (use) {
+        const AtomInfo &in = a.info[a.list_sorted[e]];
+        double rb[3];
+        g.im = gen_images(in, d, g0, rb);
+        g.sc = sqrt(in.inv2s2);
+        // finite, so that the points outside the sphere add zero
+        g.w = fmin(fmax(in.w, -1.7976931348623157e308), 1.7976931348623157e308);
+    }
+    g.run = gen_run(d.tri[5] * g.sc, qc);
+    return g;
+}
+
+// s of the lane's row and tm of its run at offset ok, for an image of a
+// displacement p; false when the image reaches none of the wavefront's points
+__device__ __forceinline__ bool gen_row(const ProbDesc &d, const GenRows &rows, const double p[3], double sc, double c, int ok,
+                                        double qc, double &d1, double &d2, double &s, double &tm)
+{
+    d1 = p[0] + rows.r[0];
+    d2 = p[1] + rows.r[1];
+    const double u1 = d1 * sc, u2 = d2 * sc;
+    s = rows.inside ? u1 * u1 + u2 * u2 : HUGE_VAL;
+    tm = (p[2] + rows.r[2] + (ok + 4) * d.tri[5]) * sc;
+    const double far = fmax(fabs(tm) - 4.0 * c, 0.0);
+    return __any(fma(far, far, s) <= qc);
+}
+
+// splat: one workgroup per brick and run of points, its wavefronts taking the
+// list's entries in turn; their sums are added in a fixed order
+__global__ __launch_bounds__(64 * kWays) void k_splat_general64(SplatArgs a)
+{
+    __shared__ double part[kWays - 1][kRun][64];
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int item = xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t b = item / kSeg;
+    const int prob = brick_prob(a, b);
+    const ProbDesc &d = a.desc[prob];
+    const GenRows rows = gen_rows(d, brick_pos(d, b), lane);
+    const int o[3] = {0, 0, kRun * (item % kSeg)};
+    if (rows.g0[2] + o[2] >= d.dims[2]) return;
+    const int64_t off = a.offsets[b];
+    const int cnt = int(a.offsets[b + 1] - off);
+    const double qc = 0.5 * a.cutoff * a.cutoff;
+    double acc[kRun];
+#pragma unroll
+    for (int k = 0; k < kRun; ++k) acc[k] = 0.0;
+    for (int c0 = 0; c0 < cnt; c0 += 64 * kWays) {
+        const int mye = c0 + lane * kWays + wave;
+        const GenAtom64 mine = gen_atom64(a, d, rows.g0, off + mye, mye < cnt, qc);
+        for (int i = 0; __any(i < mine.im.count); ++i) {
+            GenShift sh;
+            bool hit = false;
+            if (i < mine.im.count) {
+                sh = gen_shift(mine.im, d, i);
+                hit = box_distance2(d, sh.p, o, 7.0, 7.0, kRun - 1) * mine.sc * mine.sc <= kBoxMargin * qc;
+            }
+            uint64_t todo = __ballot(hit);
+            while (todo) {
+                const int q = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const double p[3] = {lane_value(sh.p[0], q), lane_value(sh.p[1], q), lane_value(sh.p[2], q)};
+                const GenRun rn = lane_run(mine.run, q);
+                double d1, d2, s, tm;
+                if (!gen_row(d, rows, p, lane_value(mine.sc, q), rn.c, o[2], qc, d1, d2, s, tm)) continue;
+                double t[kRun], e[kRun];
+                bool in[kRun];
+                gen_exps(rn, s, tm, qc, t, in, e);
+                const double w = lane_value(mine.w, q);
+#pragma unroll
+                for (int j = 0; j < kRun; ++j) acc[j] += w * (in[j] ? e[j] : 0.0);
             }
         }
-        __syncthreads();
-        for (int e = t; e < nc * 3; e += kGenThreads) {
-            const int q = e / 3, x = e - q * 3;
-            double v = 0.0;
-            for (int w = 0; w < kGenThreads / 64; ++w) v += double(red[w][q][x]);
-            const int64_t slot = off + c0 + q;
-            if (slot < a.capacity) a.bpart[slot * 3 + x] = v;
+    }
+    if (wave > 0)
+#pragma unroll
+        for (int k = 0; k < kRun; ++k) part[wave - 1][k][lane] = acc[k];
+    __syncthreads();
+    if (wave > 0 || !rows.inside) return;
+    const double bg = a.subtract_background ? a.qsum[prob] / (d.dv * double(d.npts)) : 0.0;
+    double *out = reinterpret_cast<double *>(a.rho) + d.grid_off + rows.row + o[2];
+    const int kn = d.dims[2] - rows.g0[2] - o[2];
+#pragma unroll
+    for (int k = 0; k < kRun; ++k) {
+        double v = acc[k];
+        for (int w = 0; w < kWays - 1; ++w) v += part[w][k][lane];
+        if (k < kn) out[k] = v - bg;
+    }
+}
+
+// the wavefront's sum, in lane 63 (every lane active; a fixed order): within
+// rows of 16 lanes (row shifts by 1, 2, 4, 8), then across the rows (row
+// broadcasts of lanes 15 and 31)
+__device__ __forceinline__ double wave_sum63(double x)
+{
+    x = dpp_plus<0x111, 0xf>(x);
+    x = dpp_plus<0x112, 0xf>(x);
+    x = dpp_plus<0x114, 0xf>(x);
+    x = dpp_plus<0x118, 0xf>(x);
+    x = dpp_plus<0x142, 0xa>(x);
+    x = dpp_plus<0x143, 0xc>(x);
+    return x;
+}
+
+// adjoint: as in FP32, grad_rho of the brick in LDS and each wavefront with
+// list entries of its own; the sums, in the triangular frame, are turned to
+// Cartesian axes at the end
+__global__ __launch_bounds__(64 * kWays) void k_adjoint_general64(SplatArgs a, int split)
+{
+    __shared__ double gr[kSeg][kRun][64];
+    static_assert(kSeg == kWays, "one wavefront loads each run");
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int64_t b = blockIdx.x / split;
+    const int share = blockIdx.x - int(b) * split;
+    const int prob = brick_prob(a, b);
+    const ProbDesc &d = a.desc[prob];
+    const GenRows rows = gen_rows(d, brick_pos(d, b), lane);
+    const int64_t off = a.offsets[b];
+    const int cnt = int(a.offsets[b + 1] - off);
+    const int ways = kWays * split, way = kWays * share + wave;
+    if (kWays * share >= cnt) return;
+    {
+        // zero outside the grid
+        const int k0 = kRun * wave;
+        const double *src = reinterpret_cast<const double *>(a.grad_rho) + d.grid_off + (rows.inside ? rows.row : 0);
+#pragma unroll
+        for (int k = 0; k < kRun; ++k)
+            gr[wave][k][lane] = rows.inside && rows.g0[2] + k0 + k < d.dims[2] ? src[k0 + k] : 0.0;
+    }
+    __syncthreads();
+    const double qc = 0.5 * a.cutoff * a.cutoff;
+    for (int c0 = 0; c0 < cnt; c0 += 64 * ways) {
+        const int mye = c0 + lane * ways + way;
+        const GenAtom64 mine = gen_atom64(a, d, rows.g0, off + mye, mye < cnt, qc);
+        for (int q = 0; q < 64 && c0 + q * ways + way < cnt; ++q) {
+            const GenRun rn = lane_run(mine.run, q);
+            const double sc = lane_value(mine.sc, q);
+            GenImages im;
+            im.count = lane_value(mine.im.count, q);
+            for (int x = 0; x < 3; ++x) {
+                im.r[x] = lane_value(mine.im.r[x], q);
+                im.u0[x] = lane_value(mine.im.u0[x], q);
+                im.mc[x] = lane_value(mine.im.mc[x], q);
+            }
+            double f1 = 0.0, f2 = 0.0, f3 = 0.0;
+            for (int i = 0; i < im.count; ++i) {
+                const GenShift sh = gen_shift(im, d, i);
+                // runs the sphere reaches: lane l < kSeg tests run l
+                const int ol[3] = {0, 0, kRun * (lane & (kSeg - 1))};
+                const uint32_t reach =
+                    uint32_t(__ballot(box_distance2(d, sh.p, ol, 7.0, 7.0, kRun - 1) * sc * sc <= kBoxMargin * qc));
+#pragma unroll 1
+                for (int seg = 0; seg < kSeg; ++seg) {
+                    if (!((reach >> seg) & 1u) || rows.g0[2] + kRun * seg >= d.dims[2]) continue;
+                    double d1, d2, s, tm;
+                    if (!gen_row(d, rows, sh.p, sc, rn.c, kRun * seg, qc, d1, d2, s, tm)) continue;
+                    double t[kRun], e[kRun];
+                    bool in[kRun];
+                    gen_exps(rn, s, tm, qc, t, in, e);
+                    double fs = 0.0;
+#pragma unroll
+                    for (int j = 0; j < kRun; ++j) {
+                        // (selected after the product: a non-finite grad_rho
+                        // beyond the sphere does not reach the atom)
+                        const double g = in[j] ? gr[seg][j][lane] * e[j] : 0.0;
+                        fs += g;
+                        f3 += g * t[j];
+                    }
+                    f1 += fs * d1;
+                    f2 += fs * d2;
+                }
+            }
+            f1 = wave_sum63(f1);
+            f2 = wave_sum63(f2);
+            f3 = wave_sum63(f3) / sc;
+            const int64_t slot = off + c0 + q * ways + way;
+            if (lane == 63 && slot < a.capacity)
+                for (int x = 0; x < 3; ++x)
+                    a.bpart[slot * 3 + x] = f1 * d.frame[x] + f2 * d.frame[3 + x] + f3 * d.frame[6 + x];
         }
-        __syncthreads();
     }
 }
 
 hipError_t run_gather_general(const SplatArgs &a, hipStream_t s)
 {
+    const int nb = int(a.nbricks_total);
     if (a.fp64)
-        hipLaunchKernelGGL(k_splat_general<double>, dim3(int(a.nbricks_total)), dim3(kGenThreads), 0, s, a);
+        hipLaunchKernelGGL(k_splat_general64, dim3(nb * kSeg), dim3(64 * kWays), 0, s, a);
+    else if (nb < kFewBricks)
+        hipLaunchKernelGGL(k_splat_general32<4>, dim3(nb * 8), dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL(k_splat_general<float>, dim3(int(a.nbricks_total)), dim3(kGenThreads), 0, s, a);
+        hipLaunchKernelGGL(k_splat_general32<16>, dim3(nb * 2), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t run_adjoint_general(const SplatArgs &a, hipStream_t s)
 {
-    if (a.fp64)
-        hipLaunchKernelGGL(k_adjoint_general<double>, dim3(int(a.nbricks_total)), dim3(kGenThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_adjoint_general<float>, dim3(int(a.nbricks_total)), dim3(kGenThreads), 0, s, a);
+    const int nb = int(a.nbricks_total);
+    const int split = nb < kFewBricks ? 8 : 2;
+    if (a.fp64) {
+        hipLaunchKernelGGL(k_adjoint_general64, dim3(nb * split), dim3(64 * kWays), 0, s, a, split);
+    } else {
+        if (a.many)
+            hipLaunchKernelGGL(k_adjoint_general32<true>, dim3(nb * split), dim3(256), 0, s, a, split);
+        else
+            hipLaunchKernelGGL(k_adjoint_general32<false>, dim3(nb * split), dim3(256), 0, s, a, split);
+    }
     return hipGetLastError();
 }
 

@@ -154,6 +154,59 @@ def test_splat_adjoint_parity(H, oracle_mod, prec, case):
     assert err <= (1e-10 if prec == "fp64" else 1e-5)
 
 
+# cells and grids where the general-cell kernels can go wrong: bricks with one
+# point left over, axes shorter than a brick, a grid too coarse for the FP64
+# kernels' factored exponentials, lists longer than every chunk, negative and
+# left-handed rows, and windows that hold several images
+GENERAL_EDGES = {
+    "remainders": ([[9.0, 0.5, 0.0], [2.5, 8.0, 0.3], [-1.5, 2.0, 10.5]], (18, 35, 36), 25, (0.6, 1.0)),
+    "short_axes": ([[7.0, 0.0, 0.0], [1.5, 8.0, 0.0], [-1.0, 1.0, 9.0]], (7, 10, 21), 9, (0.8, 1.0)),
+    "coarse": ([[9.0, 0.0, 0.0], [2.0, 9.0, 0.0], [1.0, -2.0, 9.5]], (14, 15, 14), 12, (0.6, 0.7)),
+    "long_lists": ([[12.0, 0.0, 0.0], [3.0, 12.0, 0.0], [-2.0, 3.0, 12.0]], (40, 36, 48), 700, (0.6, 0.9)),
+    "negative_row": ([[-9.0, 0.0, 0.0], [0.0, 10.0, 0.0], [0.0, 0.0, 11.0]], (32, 30, 64), 20, (0.6, 1.0)),
+    "left_handed": ([[0.0, 0.0, 9.0], [1.0, 10.0, 0.0], [11.0, 0.0, -2.0]], (27, 48, 40), 20, (0.6, 1.0)),
+    "many_images": ([[4.0, 0.0, 0.0], [1.0, 4.5, 0.0], [-1.0, 0.5, 5.0]], (20, 18, 25), 6, (0.8, 1.0)),
+}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("case", list(GENERAL_EDGES))
+def test_general_cell_edges(H, oracle_mod, prec, case):
+    """Density and forces in cells that are not diagonal-positive against the
+    oracle (tolerances of the other parity tests); a non-finite gradient value
+    beyond an atom's sphere leaves that atom's force bit for bit."""
+    say("case general cell edges", prec, case)
+    cell, dims, natoms, sig_range = GENERAL_EDGES[case]
+    p = inputs.small_cell_problem(cell, dims, natoms, seed=41, sig=sig_range)
+    plan = H.Plan(p.cell, p.dims, precision=prec, max_atoms=p.natoms)
+    pos, Z, sig = _atoms(p)
+    rho = plan.splat(pos, Z, sig).double().cpu().numpy()
+    ref = oracle_mod.splat(p.cell.reshape(9), p.dims, p.pos, p.Z, p.sigma)
+    nb = oracle_mod.splat(p.cell.reshape(9), p.dims, p.pos, p.Z, p.sigma, subtract_background=False)
+    e = np.abs(rho - ref).max() / np.abs(nb).max()
+    g = oracle_mod.poisson(p.cell.reshape(9), ref)[0].astype(np.float32 if prec == "fp32" else np.float64)
+    got = plan.splat_adjoint(pos, Z, sig, to_dev(g, plan.dtype)).cpu().numpy()
+    want = oracle_mod.splat_adjoint(p.cell.reshape(9), p.pos, p.Z, p.sigma, g.astype(np.float64))
+    ef = np.abs(got - want).max() / np.abs(want).max()
+    say("  rho max-rel %.3e  grad max-rel %.3e" % (e, ef))
+    assert plan.device_status() == 0
+    assert e <= (1e-13 if prec == "fp64" else 1e-6)
+    assert ef <= (1e-10 if prec == "fp64" else 1e-5)
+    # one narrow atom, a NaN at the grid point farthest from it
+    far = inputs.small_cell_problem(cell, dims, 1, seed=43, sig=(0.3, 0.3))
+    one = H.Plan(p.cell, p.dims, precision=prec, max_atoms=1, cutoff_sigmas=4.0)
+    pos, Z, sig = _atoms(far)
+    ix = np.stack(np.meshgrid(*[np.arange(n) / n for n in dims], indexing="ij"), -1)
+    f = ix - np.asarray(far.pos[0]) @ np.linalg.inv(p.cell)
+    f -= np.round(f)
+    shifts = [np.array(s) for s in itertools.product((-1, 0, 1), repeat=3)]
+    dist = np.min([np.linalg.norm((f + s) @ p.cell, axis=-1) for s in shifts], axis=0)
+    assert dist.max() > 4.0 * 0.3 * 1.01
+    clean = one.splat_adjoint(pos, Z, sig, to_dev(g, plan.dtype))
+    g[np.unravel_index(np.argmax(dist), dims)] = np.nan
+    assert torch.equal(one.splat_adjoint(pos, Z, sig, to_dev(g, plan.dtype)), clean)
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_many_atoms_one_problem(H, oracle_mod, prec):
     """33,000 atoms in one problem, more than the binning's bitmap ranks cover
