@@ -325,8 +325,15 @@ void rebuild_launches(hartree_plan p)
     for (int x = 0; x < 3; ++x) multi[x] = multi_axis(p, x);
     for (int q = 0; q < p->nprob; ++q) {
         ProbDesc &d = p->desc[q];
-        const auto *c = &p->cfg[3 * q];
-        for (int x = 0; x < 3; ++x) d.ax[x].cplan = c[x].plan;
+        hartree_plan_s::AxisCfg c[3];
+        for (int x = 0; x < 3; ++x) {
+            c[x] = p->cfg[3 * q + x];
+            d.ax[x].cplan = c[x].plan;
+            if (c[x].plan >= 0) continue;
+            runtime_tile(p->fp64, x, d.dims[x], c[x].p_log2, c[x].pad);
+            const int *r = d.ax[x].radix;
+            if (std::find(r, r + d.ax[x].nstages, 16) != r + d.ax[x].nstages) c[x].plan = kRuntimeWide;
+        }
         const int pa = 1 << c[0].p_log2, pb = 1 << c[1].p_log2, pc = 1 << c[2].p_log2;
         const int64_t rows = int64_t(d.dims[0]) * d.dims[1];
         const int64_t t1 = (rows + 2 * pc - 1) / (2 * pc);
@@ -513,7 +520,13 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
                 pad = pass_default_pad(p->fp64, N[x], d.ax[x].radix, d.ax[x].nstages, lp);
                 if (pass_tile_lds(p->fp64, N[x], lp, pad) > pass_tile_lds(p->fp64, N[x], lp, 1)) pad = 1;
             }
-            p->cfg.push_back({find_plan(d.ax[x].radix, d.ax[x].nstages), lp, pad});
+            const int plan = find_plan(d.ax[x].radix, d.ax[x].nstages);
+            // (no more pencils than set_config accepts)
+            if (plan < 0)
+                p->cfg.push_back({-1, std::min(runtime_default_p_log2(p->fp64, x, N[x]),
+                                               pass_p_log2(p->fp64, N[x], d.ax[x].radix, d.ax[x].nstages, 64)), 0});
+            else
+                p->cfg.push_back({plan, lp, pad});
         }
         // tile counts at one pencil per workgroup bound every choice
         const int64_t rows = int64_t(N[0]) * N[1];

@@ -2,7 +2,7 @@
 // radix kernel (one translation unit per pass and precision so the build
 // compiles them in parallel), and per plan kernels for tiles of 4, 8 and 16
 // pencils with no pitch pad, whose tile shape is compiled in.
-#include "fft_passes.hpp"
+#include "fft_runtime.hpp"
 
 namespace hartree {
 namespace {
@@ -43,7 +43,8 @@ hipError_t run_a_f32(int plan, int maxn, int grid, hipStream_t s, const PassArgs
             return launch_pass(k_fft_a_multi<float, 0>, grid, multi_auto_lds<float>(0, maxn), s, a);
         return hipErrorInvalidValue;
     }
-    if (plan < 0 || plan >= int(sizeof(kTable) / sizeof(kTable[0]))) return launch_one<0, 0, 0, 0>(grid, lds, s, a);
+    if (plan < 0 || plan >= int(sizeof(kTable) / sizeof(kTable[0])))
+        return launch_a_rt<float>(plan == kRuntimeWide, maxn, grid, s, a);
     // the compiled tiles address their pencils with 32-bit lane offsets
     if (a.pad == 0 && lane_offsets_fit<float>(a)) {
         if (a.p_log2 == 2) return kFixed4[plan](grid, lds, s, a);

@@ -2,7 +2,7 @@
 // radix kernel (one translation unit per pass and precision so the build
 // compiles them in parallel), and per plan kernels for tiles of 2, 4 and 8
 // pencils whose tile shape and pencil length are compiled in.
-#include "fft_passes.hpp"
+#include "fft_runtime.hpp"
 
 namespace hartree {
 namespace {
@@ -40,7 +40,7 @@ hipError_t run_c2r_f32(int plan, int maxn, int grid, hipStream_t s, const PassAr
         return hipErrorInvalidValue;
     }
     if (plan < 0 || plan >= int(sizeof(kTable) / sizeof(kTable[0])))
-        return launch_one<0, 0, 0, 0, 0>(grid, lds, s, a);
+        return launch_c2r_rt<float>(plan == kRuntimeWide, maxn, grid, s, a);
     if (a.pad == 0 && a.p_log2 == 1) return kFixed2[plan](grid, lds, s, a);
     if (a.pad == 0 && a.p_log2 == 2) return kFixed4[plan](grid, lds, s, a);
     if (a.pad == 0 && a.p_log2 == 3) return kFixed8[plan](grid, lds, s, a);

@@ -1,7 +1,7 @@
 // P5 (c2r along c) kernels, FP64: one per radix plan of HARTREE_PLANS plus the run-time
 // radix kernel (one translation unit per pass and precision so the build
 // compiles them in parallel).
-#include "fft_passes.hpp"
+#include "fft_runtime.hpp"
 
 namespace hartree {
 namespace {
@@ -19,7 +19,8 @@ hipError_t run_c2r_f64(int plan, int maxn, int grid, hipStream_t s, const PassAr
 {
     const size_t lds = pass_lds_bytes<double>(a, maxn);
     if (plan == kMultiPlan) return hipErrorInvalidValue;  // multi-plan launches are FP32 only
-    if (plan < 0 || plan >= int(sizeof(kTable) / sizeof(kTable[0]))) return launch_one<0, 0, 0, 0>(grid, lds, s, a);
+    if (plan < 0 || plan >= int(sizeof(kTable) / sizeof(kTable[0])))
+        return launch_c2r_rt<double>(plan == kRuntimeWide, maxn, grid, s, a);
     return kTable[plan](grid, lds, s, a);
 }
 }  // namespace hartree

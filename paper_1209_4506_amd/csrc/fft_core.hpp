@@ -390,55 +390,11 @@ __host__ __device__ constexpr int stage_maxb(int R)
     return (sizeof(T) == 4 ? 32 : 21) / R > 0 ? (sizeof(T) == 4 ? 32 : 21) / R : 1;
 }
 
-// One Stockham stage.  Src and Dst are pencil accessors; when both are the
-// same tile, SYNC separates all reads from all writes.
-template <typename T, int R, int MAXB, bool FIRST, bool SYNC, typename Src, typename Dst>
-__device__ __forceinline__ void stage(const Src &src, Dst &dst, const Cx<T> *tw, int n, int twstride,
-                                      const FastDiv &nsd, int tip, int tpp)
-{
-    const int nb = n / R;
-    Cx<T> v[MAXB][R];
-#pragma unroll
-    for (int m = 0; m < MAXB; ++m) {
-        const int j = tip + m * tpp;
-        if (j < nb) {
-#pragma unroll
-            for (int q = 0; q < R; ++q) v[m][q] = src.load_at(m * tpp + q * nb, tip);
-        }
-    }
-    if (SYNC) __syncthreads();
-#pragma unroll
-    for (int m = 0; m < MAXB; ++m) {
-        const int j = tip + m * tpp;
-        if (j < nb) {
-            int jd = j, k = 0, ns = 1;
-            if (!FIRST) {
-                ns = int(nsd.d);
-                jd = int(fdiv(uint32_t(j), nsd));
-                k = j - jd * ns;
-                // twiddle indices stay below n <= 2^24: 24-bit products
-                const int tstep = __mul24(k, twstride);
-#pragma unroll
-                for (int q = 1; q < R; ++q) v[m][q] = cmul(v[m][q], tw[__mul24(q, tstep)]);
-            }
-            butterfly<T, R, false>(v[m]);
-            if constexpr (Dst::kLds) {
-                const int base = jd * ns * R + k;
-#pragma unroll
-                for (int q = 0; q < R; ++q) dst.store(base + q * ns, v[m][q]);
-            } else {
-                // only the last stage writes global memory: ns = n / R,
-                // so jd = 0 and k = j
-#pragma unroll
-                for (int q = 0; q < R; ++q) dst.store_at(m * tpp + q * ns, tip, v[m][q]);
-            }
-        }
-    }
-}
-
-// The same stage with the length, the stride of its outputs (ns, the
-// product of the earlier radices) and its twiddle stride known at compile
-// time (the compiled radix plans): index arithmetic folds into constants.
+// One Stockham stage of a compiled radix plan: the length, the stride of its
+// outputs (ns, the product of the earlier radices) and its twiddle stride are
+// known at compile time, so index arithmetic folds into constants.  Src and
+// Dst are pencil accessors; when both are the same tile, SYNC separates all
+// reads from all writes.
 // INV: the inverse transform's stage (conjugate twiddles and butterflies).
 template <typename T, int R, int MAXB, bool FIRST, bool SYNC, int NB, int NS, int TWS, bool INV, typename Src,
           typename Dst>
@@ -499,64 +455,14 @@ __device__ __forceinline__ void stage_ct(const Src &src, Dst &dst, const Cx<T> *
     }
 }
 
-// Dispatch one stage on its runtime radix.
-template <typename T, bool FIRST, bool SYNC, typename Src, typename Dst>
-__device__ __forceinline__ void stage_any(int r, const Src &src, Dst &dst, const Cx<T> *tw, int n, int twstride,
-                                          const FastDiv &nsd, int tip, int tpp)
-{
-#define HARTREE_STAGE(RR) \
-    stage<T, RR, stage_maxb<T>(RR), FIRST, SYNC>(src, dst, tw, n, twstride, nsd, tip, tpp)
-    switch (r) {
-    case 2: HARTREE_STAGE(2); break;
-    case 3: HARTREE_STAGE(3); break;
-    case 4: HARTREE_STAGE(4); break;
-    case 5: HARTREE_STAGE(5); break;
-    case 7: HARTREE_STAGE(7); break;
-    case 8: HARTREE_STAGE(8); break;
-    case 9: HARTREE_STAGE(9); break;
-    case 10: HARTREE_STAGE(10); break;
-    case 16: HARTREE_STAGE(16); break;
-    default: break;  // not produced by the plan search
-    }
-#undef HARTREE_STAGE
-}
-
-// Forward transform of a tile whose first stage reads from `src` and whose
-// last stage writes to `dst` (either may be global memory or the LDS tile;
-// conjugating accessors turn it into the inverse); the stages in between run
-// in place on the LDS tile `lds`.  A single-stage length runs its stage into
-// the tile and then copies it to dst.  On return every thread has finished
-// writing; the caller synchronizes before reading the LDS tile.
-template <typename T, typename Src, typename Dst, typename L>
-__device__ __forceinline__ void fft_pencils(const Src &src, Dst &dst, const L &lds, const Cx<T> *tw,
-                                            const AxisPlan &ap, int tip, int tpp)
-{
-    const int n = ap.n;
-    const int S = ap.nstages;
-    L l = lds;
-    l.cj = false;
-    // a stage that writes where the workgroup still reads (the LDS tile)
-    // separates its reads from its writes with a barrier
-    stage_any<T, true, Src::kLds>(ap.radix[0], src, l, tw, n, ap.twstride[0], ap.ns[0], tip, tpp);
-    __syncthreads();
-    if (S == 1) {
-        for (int u = 0; u + tip < n; u += tpp) dst.store_at(u, tip, l.load(u + tip));
-        return;
-    }
-    for (int s = 1; s + 1 < S; ++s) {
-        stage_any<T, false, true>(ap.radix[s], l, l, tw, n, ap.twstride[s], ap.ns[s], tip, tpp);
-        __syncthreads();
-    }
-    const int s = S - 1;
-    stage_any<T, false, Dst::kLds>(ap.radix[s], l, dst, tw, n, ap.twstride[s], ap.ns[s], tip, tpp);
-}
-
-// The same transform with the stage radices fixed at compile time (R1..R3 = 0
-// for absent stages).  Each stage then gets registers sized for its own
-// radix; a kernel that switches between radices at run time (fft_pencils)
-// must hold registers for the largest case in every stage, which costs
-// occupancy.  INV: the inverse transform (unnormalized), with no
-// conjugation of its input or output.
+// Transform of a tile whose first stage reads from `src` and whose last stage
+// writes to `dst` (either may be global memory or the LDS tile); the stages in
+// between run in place on the LDS tile `lds`.  A single-stage length runs its
+// stage into the tile and then copies it to dst.  On return every thread has
+// finished writing; the caller synchronizes before reading the LDS tile.
+// The stage radices are fixed at compile time (R1..R3 = 0 for absent stages),
+// so each stage gets registers sized for its own radix.  INV: the inverse
+// transform (unnormalized), with no conjugation of its input or output.
 template <typename T, int R0, int R1, int R2, int R3, bool INV = false, typename Src, typename Dst, typename L>
 __device__ __forceinline__ void fft_static(const Src &src, Dst &dst, const L &lds, const Cx<T> *tw,
                                            const AxisPlan &ap, int tip, int tpp)
@@ -590,17 +496,6 @@ __device__ __forceinline__ void fft_static(const Src &src, Dst &dst, const L &ld
     }
 }
 
-// Either form: R0 = 0 selects the run-time radix switch.
-template <typename T, int R0, int R1, int R2, int R3, typename Src, typename Dst, typename L>
-__device__ __forceinline__ void fft_any(const Src &src, Dst &dst, const L &lds, const Cx<T> *tw,
-                                        const AxisPlan &ap, int tip, int tpp)
-{
-    if constexpr (R0 == 0)
-        fft_pencils<T>(src, dst, lds, tw, ap, tip, tpp);
-    else
-        fft_static<T, R0, R1, R2, R3>(src, dst, lds, tw, ap, tip, tpp);
-}
-
 // Radix plans with their own compiled kernels: the stage radices that the
 // plan search picks for common lengths (32, 48, 60, 64, 72, 90, 96, 120, 128,
 // 150, 160, 180, 192, 200, 210, 240, 256, 288, 300, 320, 360, 384, 400, 420,
@@ -613,7 +508,7 @@ __device__ __forceinline__ void fft_any(const Src &src, Dst &dst, const L &lds, 
 // first stages for 360, whose 30 butterflies per pencil take one round on 32
 // threads (radix 10's 36 take two).  Entries are only ever appended, so that
 // stored tuner choices keep their meaning.
-// Other lengths run the run-time radix switch.
+// Other lengths run the run-time radix kernels (fft_runtime.hpp).
 #define HARTREE_PLANS(X)                                                                                  \
     X(8, 4, 0, 0) X(16, 3, 0, 0) X(5, 4, 3, 0) X(8, 8, 0, 0) X(9, 8, 0, 0) X(10, 9, 0, 0) X(8, 4, 3, 0)   \
     X(8, 5, 3, 0) X(16, 8, 0, 0) X(10, 5, 3, 0) X(16, 10, 0, 0) X(9, 5, 4, 0) X(8, 8, 3, 0)              \

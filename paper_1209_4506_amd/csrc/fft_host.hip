@@ -133,6 +133,46 @@ int pass_p_log2(int fp64, int n, const int *radix, int nstages, int max_p)
     return l;
 }
 
+// a CU's LDS, less what the kernels hold beside the tile
+constexpr size_t kCuLds = 160 * 1024 - 256;
+
+size_t runtime_lds(int fp64, int x, int n, int p_log2, int pad, bool &twg)
+{
+    const size_t cx = fp64 ? 16 : 8, P = size_t(1) << p_log2;
+    const size_t copy = x == 2 ? P * size_t(row_pitch(n)) : (P + size_t(pad)) * size_t(n);
+    twg = cx * (2 * copy + size_t(n)) > kCuLds;
+    return cx * (2 * copy + (twg ? 0 : size_t(n)));
+}
+
+// the tile a run-time radix pass takes for a requested one: the pad, then
+// pencils, given up until two copies and the twiddles fit (a single pencil of
+// the longest lengths in double reads its twiddles from global memory)
+void runtime_tile(int fp64, int x, int n, int &p_log2, int &pad)
+{
+    bool twg;
+    while (runtime_lds(fp64, x, n, p_log2, pad, twg) > kCuLds || twg) {
+        if (pad > 0) pad = 0;
+        else if (p_log2 > 0) --p_log2;
+        else break;
+    }
+}
+
+// Default pencils per tile of the run-time radix passes: as many as leave a
+// CU room for two to four such workgroups, as its kernel's registers allow,
+// and no more than pay.  Measured (us, FP32 unless noted):
+//   a  n = 75: 8 34.8, 16 26.0, 32 22.8; n = 252: 4 82, 8 62, 16 75 (past a third
+//      of the LDS); FP64, two wavefronts per SIMD: n = 135: 8 42, 16 34, 32 39
+//   b  n = 168: 4 15.1, 8 12.6, 16 16.7; n = 625: 2 20.4, 4 18.9, 8 27.5
+//   c  n = 189: 4 16.9, 8 16.4, 16 21.4; n = 280: 2 64, 4 47, 8 57 (past a fourth)
+int runtime_default_p_log2(int fp64, int x, int n)
+{
+    bool twg;
+    int lp = x == 0 ? (fp64 ? 4 : 5) : 3;
+    const size_t most = kCuLds / (x == 0 ? (fp64 ? 2 : 3) : (x == 1 || fp64 ? 3 : 4));
+    while (lp > 0 && (runtime_lds(fp64, x, n, lp, 0, twg) > most || twg)) --lp;
+    return lp;
+}
+
 #define HARTREE_ROW(R0, R1, R2, R3) {R0, R1, R2, R3},
 static const int kPlanTable[][4] = {HARTREE_PLANS(HARTREE_ROW)};
 #undef HARTREE_ROW

@@ -270,7 +270,7 @@ __device__ __forceinline__ void r2c_tile(const PassArgs &a, int prob, int tile)
         const LdsRealPairIn<T> in{blk + 2 * q * n, n};
         if (d.ax[2].nstages > 0) {
             LdsRow<T> out = lr;
-            fft_any<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
+            fft_static<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
         } else if (tip == 0) {
             lr.store(0, in.load(0));
         }
@@ -286,7 +286,7 @@ __device__ __forceinline__ void r2c_tile(const PassArgs &a, int prob, int tile)
         in.s1 = scale * in.w1;
         if (d.ax[2].nstages > 0) {
             LdsRow<T> out = lr;
-            fft_any<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
+            fft_static<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
         } else if (tip == 0) {
             lr.store(0, in.load(0));
         }
@@ -374,7 +374,7 @@ __device__ __forceinline__ void c2r_tile(const PassArgs &a, int prob, int tile)
         // all precede the first stage's barrier
         const LdsRealPairOut<T> out{reinterpret_cast<T *>(blk) + 2 * q * n, n};
         if (d.ax[2].nstages > 0) {
-            fft_any<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
+            fft_static<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
         } else if (tip == 0) {
             out.store(0, in.load(0));
         }
@@ -396,7 +396,7 @@ __device__ __forceinline__ void c2r_tile(const PassArgs &a, int prob, int tile)
         out.v0 = v0;
         out.v1 = v1;
         if (d.ax[2].nstages > 0) {
-            fft_any<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
+            fft_static<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
         } else if (tip == 0) {
             out.store(0, in.load(0));
         }
@@ -440,7 +440,7 @@ __device__ __forceinline__ void fft_b_tile(const PassArgs &a, int prob, int tile
     Cx<T> *g = reinterpret_cast<Cx<T> *>(a.spec) + d.spec_off + int64_t(outer) * n * nh + h0;
     GlobalPencil<T, (CP > 0)> gp{g, nh, tip * nh + (p < valid ? p : 0), p < valid, a.inv != 0};
     const LdsPencil<T> lp{buf, PP, p, false};
-    fft_any<T, R0, R1, R2, R3>(gp, gp, lp, tw, d.ax[1], tip, TPP);
+    fft_static<T, R0, R1, R2, R3>(gp, gp, lp, tw, d.ax[1], tip, TPP);
 }
 
 template <typename T, int R0, int R1, int R2, int R3, int CP = 0>
@@ -654,7 +654,7 @@ __device__ __forceinline__ void fft_a_tile(const PassArgs &a, int prob, int tile
         // length-1 axis: the multiply alone
         if (tip == 0) km.store(0, gp.load_at(0, 0));
     } else {
-        fft_any<T, R0, R1, R2, R3>(gp, km, lp, tw, d.ax[0], tip, TPP);
+        fft_static<T, R0, R1, R2, R3>(gp, km, lp, tw, d.ax[0], tip, TPP);
     }
     __syncthreads();
     if (energy) {
@@ -671,15 +671,8 @@ __device__ __forceinline__ void fft_a_tile(const PassArgs &a, int prob, int tile
     // inverse along a
     if (d.ax[0].nstages == 0) {
         if (tip == 0) gp.store_at(0, 0, lp.load(0));
-    } else if constexpr (R0 > 0) {
-        // a compiled plan: the inverse stages themselves
-        fft_static<T, R0, R1, R2, R3, true>(lp, gp, lp, tw, d.ax[0], tip, TPP);
     } else {
-        // run-time radices: the forward stages, conjugating on the way in
-        // and on the way out
-        const LdsPencil<T> lpc{buf, PP, p, true};
-        GlobalPencil<T, (CP > 0), true> gpc{g, ncol, lane, p < valid, true};
-        fft_any<T, R0, R1, R2, R3>(lpc, gpc, lp, tw, d.ax[0], tip, TPP);
+        fft_static<T, R0, R1, R2, R3, true>(lp, gp, lp, tw, d.ax[0], tip, TPP);
     }
 }
 

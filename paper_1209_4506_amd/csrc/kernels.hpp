@@ -54,6 +54,9 @@ constexpr int kMultiPlansC[kMultiPlans] = {0, 41, 2, 3, 4, 5, 6, 7, 42, 9, 43, 1
 // and 16 pencils along a and b, 4 and 8 along c
 constexpr int multi_log_p(int x, int k) { return x == 2 ? 2 + k : 3 + k; }
 constexpr int kMultiPlan = -2;
+// run-time radix launches (plan -1): those of plans with a radix-16 stage
+// carry kRuntimeWide (kernels of their own: the others need fewer registers)
+constexpr int kRuntimeWide = -3;
 // A third multi-plan shape sizes the tile per length instead: the most
 // pencils (a power of two, at most 64 along a and b, 32 along c) whose
 // points stay within 4096 (a) or 2048 (b, c), at least 8 (a, b) or 4 (c);
@@ -73,6 +76,12 @@ int pass_p_log2(int fp64, int n, const int *radix, int nstages, int max_p);
 int pass_min_tpp(int fp64, int n, const int *radix, int nstages);
 size_t pass_tile_lds(int fp64, int n, int p_log2, int pad);
 int pass_default_pad(int fp64, int n, const int *radix, int nstages, int p_log2);
+// LDS of a run-time radix tile along axis x (two copies of the tile and, unless
+// twg, the twiddle table), the tile it actually takes when the requested one
+// does not fit, and the default tile of a length without a compiled plan
+size_t runtime_lds(int fp64, int x, int n, int p_log2, int pad, bool &twg);
+void runtime_tile(int fp64, int x, int n, int &p_log2, int &pad);
+int runtime_default_p_log2(int fp64, int x, int n);
 int find_plan(const int *radix, int nstages);
 int plan_table_size();
 int plan_table_row(int id, int *radix);  // fills radix[4], returns the stage count

@@ -553,6 +553,60 @@ def test_every_compiled_plan(H, oracle_mod, prec, n):
     assert checked >= 12
 
 
+# lengths without a compiled plan: one to four stages, every radix first and
+# last, with and without radix 16, up to the longest (in FP64 the longest read
+# their twiddles from global memory)
+RUNTIME_LENGTHS = [2, 7, 9, 16, 14, 27, 63, 80, 112, 135, 144, 343, 405, 1701, 2187, 3402, 3430, 4050, 4096]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_runtime_radix_lengths(H, oracle_mod, prec, axis):
+    """The run-time radix kernels on each axis: the default tile, a single
+    pencil and the largest tile and pad that a plan accepts (more than the
+    kernel's two copies of the tile have room for), against the oracle."""
+    cell = CELLS["triclinic"]
+    ft = np.float32 if prec == "fp32" else np.float64
+    for n in RUNTIME_LENGTHS:
+        dims = [3, 5, 6]
+        dims[axis] = n
+        dims = tuple(dims)
+        plan = H.Plan(cell, dims, precision=prec, max_atoms=1)
+        base = plan.get_config()
+        assert base[0, axis, 0] == -1
+        rho = inputs.random_grid(dims, 61).astype(ft)
+        gv = inputs.random_grid(dims, 62).astype(ft)
+        V_o, _, e_recip, _ = oracle_mod.poisson(cell.reshape(9), rho.astype(np.float64))
+        G_o = oracle_mod.backward(cell.reshape(9), rho.astype(np.float64), grad_v=gv.astype(np.float64), grad_e=0.3)
+        G_e = oracle_mod.backward(cell.reshape(9), rho.astype(np.float64), grad_v=None, grad_e=0.3)
+        trials = [tuple(base[0, axis]), (-1, 0, 0)]
+        for lp, pad in itertools.product(range(8, 0, -1), (0,) if axis == 2 else (3, 0)):
+            cfg = base.copy()
+            cfg[0, axis] = (-1, lp, pad)
+            try:
+                plan.set_config(cfg)
+            except H.HartreeError:
+                continue
+            trials.append((-1, lp, pad))
+            break
+        for choice in trials:
+            say("case run-time radix", prec, dims, "axis", axis, "choice", choice)
+            cfg = base.copy()
+            cfg[0, axis] = choice
+            plan.set_config(cfg)
+            V, E = plan.solve(to_dev(rho, plan.dtype))
+            e_only = plan.energy(to_dev(rho, plan.dtype))
+            g = plan.backward(grad_v=to_dev(gv, plan.dtype), grad_e=torch.tensor([0.3], dtype=torch.float64),
+                              rho=to_dev(rho, plan.dtype))
+            ge = plan.backward(grad_v=None, grad_e=torch.tensor([0.3], dtype=torch.float64), rho=to_dev(rho, plan.dtype))
+            torch.cuda.synchronize()
+            assert rel_l2(V.double().cpu().numpy(), V_o) <= TOL[prec]["v"]
+            assert abs(float(E[0]) - e_recip) <= TOL[prec]["e"] * abs(e_recip)
+            assert float(e_only[0]) == float(E[0])
+            assert rel_l2(g.double().cpu().numpy(), G_o) <= TOL[prec]["v"]
+            assert rel_l2(ge.double().cpu().numpy(), G_e) <= TOL[prec]["v"]
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_tuned_plan_parity(H, oracle_mod, prec):
     """After hartree_plan_tune (and a config round trip) the solve and the
