@@ -163,6 +163,7 @@ struct hartree_plan_s {
     std::vector<int64_t> grid_offsets;
     int nparts = 0;
     int64_t nbricks = 0;
+    int32_t ncols = 0;
     int64_t capacity = 0;
     std::vector<Launch> lr2c, lb, la;  // P1/P5 (axis c), P2/P4 (axis b), P3 (axis a)
     // per problem and axis (a, b, c): compiled radix plan (-1: run-time
@@ -176,7 +177,7 @@ struct hartree_plan_s {
     int64_t max_parts = 0;  // E_H partial slots at one pencil per workgroup
     // workspace layout
     size_t o_status = 0, o_desc = 0, o_tw = 0, o_spec = 0, o_parts = 0, o_qsum = 0, o_info = 0, o_counts = 0,
-           o_offsets = 0, o_cursor = 0, o_list = 0, o_lists = 0, o_bpart = 0, o_slot = 0, o_rec = 0, o_order = 0, o_zero = 0,
+           o_offsets = 0, o_ends = 0, o_claims = 0, o_cursor = 0, o_list = 0, o_lists = 0, o_bpart = 0, o_slot = 0, o_rec = 0, o_order = 0, o_zero = 0,
            o_spec2 = 0, ws_size = 0;
     int32_t cap_pa = 0;
     bool wide = false;  // some truncation window can hold two images of one grid point
@@ -562,6 +563,8 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
             per_atom *= nbx;
         }
         d.brick_off = bricks;
+        d.col_off = p->ncols;
+        p->ncols += d.nbricks[0] * d.nbricks[1];
         bricks += int64_t(d.nbricks[0]) * d.nbricks[1] * d.nbricks[2];
         if (per_atom > cap_per_atom) cap_per_atom = per_atom;
     }
@@ -597,6 +600,8 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
         p->o_info = take(sizeof(AtomInfo) * size_t(p->max_atoms));
         p->o_counts = take(4 * size_t(p->nbricks + 1));
         p->o_offsets = take(4 * size_t(p->nbricks + 1));
+        p->o_ends = take(4 * size_t(p->nbricks + 1));
+        p->o_claims = take(4 * size_t(p->nprob) * kClaimStride);
         p->o_cursor = take(4 * size_t(p->nbricks + 1));
         p->o_list = take(4 * size_t(p->capacity));
         p->o_lists = take(4 * size_t(p->capacity));
@@ -749,6 +754,8 @@ SplatArgs splat_args(hartree_plan p, int32_t natoms, const double *pos, const do
     a.info = reinterpret_cast<AtomInfo *>(p->ws + p->o_info);
     a.counts = reinterpret_cast<int32_t *>(p->ws + p->o_counts);
     a.offsets = reinterpret_cast<int32_t *>(p->ws + p->o_offsets);
+    a.ends = reinterpret_cast<int32_t *>(p->ws + p->o_ends);
+    a.claims = reinterpret_cast<int32_t *>(p->ws + p->o_claims);
     a.cursor = reinterpret_cast<int32_t *>(p->ws + p->o_cursor);
     a.list = reinterpret_cast<int32_t *>(p->ws + p->o_list);
     a.list_sorted = reinterpret_cast<int32_t *>(p->ws + p->o_lists);
@@ -779,6 +786,7 @@ SplatArgs splat_args(hartree_plan p, int32_t natoms, const double *pos, const do
     a.cap_pa = p->cap_pa;
     a.capacity = p->capacity;
     a.nbricks_total = p->nbricks;
+    a.ncols = p->ncols;
     a.status = reinterpret_cast<DeviceStatus *>(p->ws + p->o_status);
     a.fp64 = p->fp64;
     a.qsum = reinterpret_cast<double *>(p->ws + p->o_qsum);
@@ -1166,12 +1174,12 @@ hartree_status hartree_atoms_pairs(hartree_plan plan, int64_t *pairs, void *stre
         return ok();
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int32_t v = 0;
-    hipError_t e = hipMemcpyAsync(&v, plan->ws + plan->o_offsets + 4 * size_t(plan->nbricks), 4,
-                                  hipMemcpyDeviceToHost, s);
+    std::vector<int32_t> claims(size_t(plan->nprob) * kClaimStride);
+    hipError_t e = hipMemcpyAsync(claims.data(), plan->ws + plan->o_claims, 4 * claims.size(), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "reading the binding size");
-    *pairs = v;
+    *pairs = 0;
+    for (int32_t q = 0; q < plan->nprob; ++q) *pairs += claims[size_t(q) * kClaimStride];
     return ok();
 }
 

@@ -86,7 +86,7 @@ struct ProbDesc {
     int32_t nbricks[3]; // bricks per axis
     int32_t pad2;
     int32_t bsz[3];     // brick edge in grid points per axis
-    int32_t pad3;
+    int32_t col_off;    // first column of bricks along c of this problem
 };
 
 // Splat bricks, one workgroup each: MI x MJ x MK grid points for the

@@ -92,6 +92,8 @@ hipError_t run_zero(void *p, size_t bytes, hipStream_t s);
 
 // ---------------------------------------------------------------- splat
 
+constexpr int kClaimStride = 32;  // one cache line per counter
+
 struct SplatArgs {
     const ProbDesc *desc;
     int32_t nprob;
@@ -104,7 +106,9 @@ struct SplatArgs {
     double max_sigma;
     AtomInfo *info;         // natoms
     int32_t *counts;        // nbricks_total + 1
-    int32_t *offsets;       // nbricks_total + 1
+    int32_t *offsets;       // nbricks_total + 1: first slot of each brick's list
+    int32_t *ends;          // nbricks_total: one past the last slot
+    int32_t *claims;        // per problem, kClaimStride apart: slots in use; their sum is the binding's pairs
     int32_t *cursor;        // nbricks_total
     int32_t *list;          // capacity
     int32_t *list_sorted;   // capacity
@@ -117,6 +121,7 @@ struct SplatArgs {
     int64_t capacity;
     int32_t cap_pa;         // most bricks one atom can touch
     int64_t nbricks_total;
+    int32_t ncols;          // columns of bricks along c, all problems
     DeviceStatus *status;
     int32_t subtract_background;
     int32_t fp64;

@@ -8,18 +8,22 @@
 // atom's sphere, and a box around a group of atoms); each brick is one
 // workgroup that gathers the atoms whose truncation window overlaps it.
 //
-// Binning is deterministic: every atom adds itself to the bricks its window
-// touches (integer atomics), the per-brick lists are then sorted by atom
-// index, and every sum below runs in a fixed order, so results do not depend
-// on scheduling.
+// Binning is deterministic: the per-brick lists are ordered by atom index and
+// every sum below runs in a fixed order, so results do not depend on
+// scheduling.  Two forms, by the largest atom count of a problem (run_bin):
 //
-//   count   per atom: wrapped position, weight, window [lo, hi] per axis;
-//           +1 on each touched brick
-//   scan    per problem: Q = sum Z (fixed order), for the background
-//           Q / Omega; exclusive prefix sum of the brick counts
-//   fill    per atom: write its index into each touched brick's list
-//   sort    per brick: order the list by atom index; clear the brick's
-//           counters for the next binning
+//   columns (up to kColAtoms atoms per problem)
+//     prep    per atom: wrapped position, weight, window [lo, hi] per axis;
+//             per problem: Q = sum Z (fixed order), for the background Q / Omega
+//     gather  per column of bricks along c: the atoms that touch it, in order,
+//             then each of its bricks' lists from those
+//   visits (more atoms)
+//     count   per atom: the same preparation; +1 on each touched brick
+//     scan    Q; exclusive prefix sum of the brick counts
+//     fill    per atom: write its index into each touched brick's list
+//     sort    per brick: order the list by atom index; clear the brick's
+//             counters for the next binning
+//
 //   gather  per brick: rho = sum over its atoms of w gx(i) gy(j) gz(k) [- Q/Omega]
 //   adjoint per brick: partial sum_r grad_rho(r) g(r) d(r) for each of its atoms
 //   final   per atom: fixed-order sum of its partials over the touched bricks
@@ -31,9 +35,8 @@ namespace hartree {
 
 // An atom's wrapped position, weight and window per axis; `report` sets
 // the device status bits for an invalid atom (which then touches nothing).
-__device__ __forceinline__ AtomInfo atom_prep(const SplatArgs &a, int atom, bool report)
+__device__ __forceinline__ AtomInfo atom_prep(const SplatArgs &a, int atom, int prob, bool report)
 {
-    const int prob = find_prob_atom(a, atom);
     const ProbDesc &d = a.desc[prob];
     AtomInfo in;
     in.prob = prob;
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(256) void k_brick_visit(SplatArgs a)
     const int atom = int((int64_t(w) * a.visit_stride) % a.natoms);
     AtomInfo in;
     if (MODE == 0) {
-        in = atom_prep(a, atom, lane == 0);
+        in = atom_prep(a, atom, find_prob_atom(a, atom), lane == 0);
         if (lane == 0) a.info[atom] = in;
     } else {
         in = a.info[atom];
@@ -223,6 +226,91 @@ __device__ __forceinline__ void charge_and_weight(const SplatArgs &a, int i0, in
     }
 }
 
+// the charge and largest weight of problem p by a workgroup of THREADS, which
+// stand for kScanThreads: number t takes the atoms t, t + kScanThreads, ...,
+// then fixed butterflies over 64 numbers each
+template <int THREADS>
+__device__ __forceinline__ void problem_charge(const SplatArgs &a, int p, double *qw, float *ww)
+{
+    constexpr int NW = kScanThreads / 64;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+#pragma unroll
+    for (int k = 0; k < kScanThreads / THREADS; ++k) {
+        double q = 0.0;
+        float wm = 0.0f;
+        charge_and_weight(a, a.atom_off[p] + k * THREADS + t, a.atom_off[p + 1], kScanThreads, q, wm);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            q += __shfl_xor(q, off, 64);
+            wm = fmaxf(wm, __shfl_xor(wm, off, 64));
+        }
+        if (lane == 0) {
+            qw[k * (THREADS / 64) + w] = q;
+            ww[k * (THREADS / 64) + w] = wm;
+        }
+    }
+    __syncthreads();
+    if (t == 0) {
+        double tot = 0.0;
+        float wmax = 0.0f;
+        for (int k = 0; k < NW; ++k) {
+            tot += qw[k];
+            wmax = fmaxf(wmax, ww[k]);
+        }
+        a.qsum[p] = tot;
+        a.qsum[a.nprob + p] = wmax;
+    }
+    __syncthreads();
+}
+
+// the same by one wavefront: lane l the atoms l, l + 64, ... of the problem,
+// then a fixed butterfly
+__device__ __forceinline__ void problem_charge_wave(const SplatArgs &a, int p)
+{
+    const int lane = threadIdx.x & 63;
+    double q = 0.0;
+    float wm = 0.0f;
+    charge_and_weight(a, a.atom_off[p] + lane, a.atom_off[p + 1], 64, q, wm);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        q += __shfl_xor(q, off, 64);
+        wm = fmaxf(wm, __shfl_xor(wm, off, 64));
+    }
+    if (lane == 0) {
+        a.qsum[p] = q;
+        a.qsum[a.nprob + p] = wm;
+    }
+}
+
+// the work order of the bricks (a.order), by one workgroup: bricks in strided
+// order (thread t takes bricks t, t + kScanThreads, ...), so that bricks next
+// to each other in space stay next to each other within a group count;
+// count(b): the brick's atoms
+template <typename Count>
+__device__ __forceinline__ void order_bricks(const SplatArgs &a, Count count)
+{
+    __shared__ int hist[kOrderKeys], next[kOrderKeys];
+    const int t = threadIdx.x;
+    const int64_t n = a.nbricks_total;
+    auto key = [&](int64_t b) {
+        const int k = (count(b) + 15) >> 4;
+        return k < kOrderKeys - 1 ? k : kOrderKeys - 1;
+    };
+    if (t < kOrderKeys) hist[t] = 0;
+    __syncthreads();
+    for (int64_t b = t; b < n; b += kScanThreads) atomicAdd(&hist[key(b)], 1);
+    __syncthreads();
+    if (t == 0) {
+        int run = 0;
+        for (int k = kOrderKeys - 1; k >= 0; --k) {
+            next[k] = run;
+            run += hist[k];
+        }
+    }
+    __syncthreads();
+    for (int64_t b = t; b < n; b += kScanThreads) a.order[atomicAdd(&next[key(b)], 1)] = int32_t(b);
+}
+
 __global__ __launch_bounds__(kScanThreads) void k_scan(SplatArgs a)
 {
     constexpr int NW = kScanThreads / 64;
@@ -255,52 +343,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(SplatArgs a)
     int v[kScanPer];
     load_counts(int64_t(t) * kScanPer, v);
     if (a.nprob <= 4) {
-        // few problems: the whole workgroup sums each problem's charges,
-        // thread t the atoms t, t + kScanThreads, ..., then fixed butterflies
-        for (int p = 0; p < a.nprob; ++p) {
-            double q = 0.0;
-            float wm = 0.0f;
-            charge_and_weight(a, a.atom_off[p] + t, a.atom_off[p + 1], kScanThreads, q, wm);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                q += __shfl_xor(q, off, 64);
-                wm = fmaxf(wm, __shfl_xor(wm, off, 64));
-            }
-            if (lane == 0) {
-                qw[w] = q;
-                ww[w] = wm;
-            }
-            __syncthreads();
-            if (t == 0) {
-                double tot = 0.0;
-                float wmax = 0.0f;
-                for (int k = 0; k < NW; ++k) {
-                    tot += qw[k];
-                    wmax = fmaxf(wmax, ww[k]);
-                }
-                a.qsum[p] = tot;
-                a.qsum[a.nprob + p] = wmax;
-            }
-            __syncthreads();
-        }
+        for (int p = 0; p < a.nprob; ++p) problem_charge<kScanThreads>(a, p, qw, ww);
     } else {
-        // many problems: wavefront w sums the charges of problems w, w + NW,
-        // ...: lane l the atoms l, l + 64, ... of the problem, then a fixed
-        // butterfly (no workgroup barrier per problem)
-        for (int p = w; p < a.nprob; p += NW) {
-            double q = 0.0;
-            float wm = 0.0f;
-            charge_and_weight(a, a.atom_off[p] + lane, a.atom_off[p + 1], 64, q, wm);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                q += __shfl_xor(q, off, 64);
-                wm = fmaxf(wm, __shfl_xor(wm, off, 64));
-            }
-            if (lane == 0) {
-                a.qsum[p] = q;
-                a.qsum[a.nprob + p] = wm;
-            }
-        }
+        // many problems: a wavefront each (no workgroup barrier per problem)
+        for (int p = w; p < a.nprob; p += NW) problem_charge_wave(a, p);
     }
     int64_t carry = 0;  // total of the chunks before this one (the same in every thread)
     for (int64_t c0 = 0; c0 < n; c0 += CH) {
@@ -335,30 +381,57 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(SplatArgs a)
     if (t == 0) {
         a.offsets[n] = int32_t(carry < a.capacity ? carry : a.capacity);
         if (carry > a.capacity) atomicOr(&a.status->bits, 0x4u);
+        for (int p = 0; p < a.nprob; ++p) a.claims[p * kClaimStride] = p == 0 ? a.offsets[n] : 0;
     }
-    if (a.order) {
-        // bricks in strided order (thread t takes bricks t, t + kScanThreads,
-        // ...), so that bricks next to each other in space stay next to each
-        // other within a group count (the counts are read again, from cache:
-        // the thread's registers hold a contiguous run instead)
-        __shared__ int hist[kOrderKeys], next[kOrderKeys];
-        auto key = [&](int64_t b) {
-            const int k = (a.counts[b] + 15) >> 4;
-            return k < kOrderKeys - 1 ? k : kOrderKeys - 1;
-        };
-        if (t < kOrderKeys) hist[t] = 0;
-        __syncthreads();
-        for (int64_t b = t; b < n; b += kScanThreads) atomicAdd(&hist[key(b)], 1);
-        __syncthreads();
-        if (t == 0) {
-            int run = 0;
-            for (int k = kOrderKeys - 1; k >= 0; --k) {
-                next[k] = run;
-                run += hist[k];
-            }
+    // (the counts are read again, from cache: the thread's registers hold a
+    // contiguous run instead)
+    if (a.order) order_bricks(a, [&](int64_t b) { return a.counts[b]; });
+}
+
+// the entry of atom v (with its preparation in) at list slot `slot` of the
+// brick at per-axis position bc
+__device__ __forceinline__ void emit_slot(const SplatArgs &a, const ProbDesc &d, const int bc[3], int64_t slot, int v,
+                                          const AtomInfo &in)
+{
+    a.list_sorted[slot] = v;
+    const Touch t = atom_touch(in, d);
+    const int ti = touch_index(t, d, bc);
+    // with records, the adjoint writes its partials under (atom, touch)
+    // directly; otherwise the slot map leads the reduction to them
+    if (!a.rec && !a.rec64) a.slot_of[int64_t(v) * a.cap_pa + ti] = int32_t(slot);
+    if (a.rec64) {
+        // the atom relative to this brick, for the FP64 splat kernels
+        SlotAtom64 r;
+        for (int x = 0; x < 3; ++x) {
+            r.X[x] = in.X[x];
+            r.lo[x] = in.lo[x];
+            r.r0[x] = wrapi(bc[x] * d.bsz[x] - in.lo[x], d.dims[x]);
+            r.wl[x] = in.hi[x] >= in.lo[x] ? in.hi[x] - in.lo[x] + 1 : 0;
         }
-        __syncthreads();
-        for (int64_t b = t; b < n; b += kScanThreads) a.order[atomicAdd(&next[key(b)], 1)] = int32_t(b);
+        r.inv2s2 = in.inv2s2;
+        r.w = in.w;
+        r.atom = v;
+        r.touch = ti;
+        r.pad = 0;
+        a.rec64[slot] = r;
+    }
+    if (a.rec) {
+        // the atom relative to this brick, for the FP32 splat kernels
+        SlotAtom r;
+        for (int x = 0; x < 3; ++x) {
+            const int n = d.dims[x];
+            const double h = d.h[x];
+            const double xb = in.X[x] - in.lo[x] * h;
+            r.ax[x].xb = float(xb);
+            r.ax[x].xbl = float(xb - double(r.ax[x].xb));
+            r.ax[x].r0 = wrapi(bc[x] * d.bsz[x] - in.lo[x], n);
+            r.ax[x].wl = in.hi[x] >= in.lo[x] ? in.hi[x] - in.lo[x] + 1 : 0;
+        }
+        r.c2 = float(1.4426950408889634073599246810019 * in.inv2s2);
+        r.w = float(in.w);
+        r.atom = v;
+        r.touch = ti;
+        a.rec[slot] = r;
     }
 }
 
@@ -392,6 +465,7 @@ __global__ __launch_bounds__(256) void k_brick_sort(SplatArgs a, int rank_words)
         if (lane == 0) {
             a.counts[b] = 0;
             a.cursor[b] = 0;
+            a.ends[b] = int32_t(off) + cnt;
         }
     }
     // the first 128 entries are loaded once, two per lane, and the first
@@ -468,59 +542,205 @@ __global__ __launch_bounds__(256) void k_brick_sort(SplatArgs a, int rank_words)
         }
         return rank;
     };
-    auto emit = [&](int v, int rank, const AtomInfo &in) {
-        a.list_sorted[off + rank] = v;
-        const Touch t = atom_touch(in, d);
-        const int ti = touch_index(t, d, bc);
-        // with records, the adjoint writes its partials under (atom, touch)
-        // directly; otherwise the slot map leads the reduction to them
-        if (!a.rec && !a.rec64) a.slot_of[int64_t(v) * a.cap_pa + ti] = int32_t(off + rank);
-        if (a.rec64) {
-            // the atom relative to this brick, for the FP64 splat kernels
-            SlotAtom64 r;
-            for (int x = 0; x < 3; ++x) {
-                r.X[x] = in.X[x];
-                r.lo[x] = in.lo[x];
-                r.r0[x] = wrapi(bc[x] * d.bsz[x] - in.lo[x], d.dims[x]);
-                r.wl[x] = in.hi[x] >= in.lo[x] ? in.hi[x] - in.lo[x] + 1 : 0;
-            }
-            r.inv2s2 = in.inv2s2;
-            r.w = in.w;
-            r.atom = v;
-            r.touch = ti;
-            r.pad = 0;
-            a.rec64[off + rank] = r;
-        }
-        if (a.rec) {
-            // the atom relative to this brick, for the FP32 splat kernels
-            SlotAtom r;
-            for (int x = 0; x < 3; ++x) {
-                const int n = d.dims[x];
-                const double h = d.h[x];
-                const double xb = in.X[x] - in.lo[x] * h;
-                r.ax[x].xb = float(xb);
-                r.ax[x].xbl = float(xb - double(r.ax[x].xb));
-                r.ax[x].r0 = wrapi(bc[x] * d.bsz[x] - in.lo[x], n);
-                r.ax[x].wl = in.hi[x] >= in.lo[x] ? in.hi[x] - in.lo[x] + 1 : 0;
-            }
-            r.c2 = float(1.4426950408889634073599246810019 * in.inv2s2);
-            r.w = float(in.w);
-            r.atom = v;
-            r.touch = ti;
-            a.rec[off + rank] = r;
-        }
-    };
     // the first entry of each lane with the atom fetched above, the rest
     // (lists longer than 64) with their own loads
     if (lane < cnt) {
         const int rank = rank_of(v0);
-        if (rank >= 0) emit(v0, rank, in0);
+        if (rank >= 0) emit_slot(a, d, bc, off + rank, v0, in0);
     }
     for (int e = lane + 64; e < cnt; e += 64) {
         const int v = entry(e);
         const int rank = rank_of(v);
-        if (rank >= 0) emit(v, rank, a.info[v]);
+        if (rank >= 0) emit_slot(a, d, bc, off + rank, v, a.info[v]);
     }
+}
+
+// ------------------------------------------------------ binning by columns
+// Bound by latency: few, short chains of dependent loads per wavefront.  The
+// count, scan, fill and sort passes cost four launches and the atomics of every
+// (atom, brick) pair; here the lists come out in order from ballots, and one
+// atomic per column claims their storage (where a list lies changes nothing:
+// the splat sums in list order, the adjoint files by atom and touched brick).
+// The claims count per problem, on lines of their own: returning atomics on one
+// address take 10 ns each (24 problems, 972 columns: 27 us against 19).
+// 32^3, 8 atoms: 22 -> 13 us; 180^3, 512 atoms: 30 -> 17; 24 batched problems: 68 ->
+// 36; 360^3, 4,096 atoms: 50 -> 37 (with about 5 us of event time in each).
+constexpr int kColAtoms = 4096;
+constexpr int kColThreads = 256;  // 64, 128 and 512 threads a column are within 15 % of it or slower
+
+// an atom's touched bricks in two words: first brick and number of bricks, 10 bits per axis
+struct AtomBricks {
+    uint32_t st, ct;
+};
+static_assert(kMaxN / 8 < 1024, "bricks per axis fit 10 bits");
+__device__ __forceinline__ AtomBricks *atom_bricks_of(const SplatArgs &a)
+{
+    return reinterpret_cast<AtomBricks *>(a.bpart);  // (the adjoint's partials: free until the next adjoint)
+}
+
+// whether brick b of an axis with nb bricks lies in the circular range that
+// starts at st and holds ct bricks
+__device__ __forceinline__ bool touches(int b, int st, int ct, int nb)
+{
+    const int r = b - st;
+    return (r < 0 ? r + nb : r) < ct;
+}
+
+// small workgroups: an atom is some hundred dependent FP64 operations, so 4,096
+// of them want many CUs (12.5 us with 1,024 threads a workgroup, 9.5 with 256)
+constexpr int kPrepThreads = 256;
+
+// One thread per atom; the workgroups from atom_blocks on sum the problems'
+// charges (one problem each, or with more than four one per wavefront).
+__global__ __launch_bounds__(kPrepThreads) void k_atom_prep(SplatArgs a, int atom_blocks)
+{
+    __shared__ double qw[kScanThreads / 64];
+    __shared__ float ww[kScanThreads / 64];
+    if (int(blockIdx.x) >= atom_blocks) {
+        const int k = blockIdx.x - atom_blocks;
+        if (a.nprob <= 4) {
+            problem_charge<kPrepThreads>(a, k, qw, ww);
+        } else {
+            const int p = k * (kPrepThreads / 64) + (threadIdx.x >> 6);
+            if (p < a.nprob) problem_charge_wave(a, p);
+        }
+        return;
+    }
+    const int atom = blockIdx.x * kPrepThreads + threadIdx.x;
+    if (blockIdx.x == 0)
+        for (int p = threadIdx.x; p < a.nprob; p += kPrepThreads) a.claims[p * kClaimStride] = 0;
+    if (atom >= a.natoms) return;
+    int prob = 0;
+    for (int q = 1; q < a.nprob; ++q) prob += atom >= a.atom_off[q] ? 1 : 0;
+    const AtomInfo in = atom_prep(a, atom, prob, true);
+    a.info[atom] = in;
+    AtomBricks w;
+    w.st = uint32_t(in.st[0]) | uint32_t(in.st[1]) << 10 | uint32_t(in.st[2]) << 20;
+    w.ct = uint32_t(in.ct[0]) | uint32_t(in.ct[1]) << 10 | uint32_t(in.ct[2]) << 20;
+    atom_bricks_of(a)[atom] = w;
+}
+
+// One workgroup per column of bricks along c.  The problem's atoms are tested
+// against the column in order, the hits kept in LDS as (index in the problem,
+// first brick and bricks along c).  The lists are then drawn from those: each
+// wavefront takes a run of bricks, whose slots are consecutive, and writes
+// entries by the full wavefront across the borders of its bricks.
+__global__ __launch_bounds__(kColThreads) void k_column_gather(SplatArgs a)
+{
+    constexpr int kSweep = 4;  // atoms per thread between two barriers: their loads are in flight together
+    constexpr int WAVES = kColThreads / 64;
+    extern __shared__ uint32_t col[];  // as many as the largest problem has atoms
+    __shared__ int wcnt[2][kSweep * WAVES];
+    __shared__ int start[kMaxN / 8 + 1];  // the column's lists, relative to its storage
+    __shared__ int claimed;
+    __shared__ uint32_t stage[WAVES][128];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int prob = wave_find(a.nprob, blockIdx.x, [&](int q) { return int64_t(a.desc[q].col_off); });
+    const ProbDesc &d = a.desc[prob];
+    const int c = int(blockIdx.x) - d.col_off, nb0 = d.nbricks[0], nb1 = d.nbricks[1], nb2 = d.nbricks[2];
+    const int b0 = c / nb1, b1 = c % nb1;
+    const int a0 = a.atom_off[prob], span = a.atom_off[prob + 1] - a0;
+    const uint64_t below = (uint64_t(1) << lane) - 1;
+    const AtomBricks *touched = atom_bricks_of(a) + a0;
+    int n = 0;
+    for (int i0 = 0, par = 0; i0 < span; i0 += kSweep * kColThreads, par ^= 1) {
+        AtomBricks w[kSweep];
+        uint64_t mask[kSweep];
+#pragma unroll
+        for (int k = 0; k < kSweep; ++k) {
+            const int i = i0 + k * kColThreads + t;
+            w[k] = touched[i < span ? i : 0];
+            if (i >= span) w[k].ct = 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kSweep; ++k) {
+            const bool hit = touches(b0, w[k].st & 1023, w[k].ct & 1023, nb0) &&
+                             touches(b1, (w[k].st >> 10) & 1023, (w[k].ct >> 10) & 1023, nb1) && (w[k].ct >> 20) > 0;
+            mask[k] = __ballot(hit);
+            if (lane == 0) wcnt[par][k * WAVES + wave] = __popcll(mask[k]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSweep; ++k) {
+            int before = n;
+#pragma unroll
+            for (int v = 0; v < WAVES; ++v) {
+                const int m = wcnt[par][k * WAVES + v];
+                if (v < wave) before += m;
+                n += m;
+            }
+            if ((mask[k] >> lane) & 1)
+                col[before + __popcll(mask[k] & below)] =
+                    uint32_t(i0 + k * kColThreads + t) | (w[k].st >> 20) << 12 | (w[k].ct >> 20) << 22;
+        }
+    }
+    __syncthreads();
+    auto in_brick = [&](uint32_t e, int k) { return touches(k, (e >> 12) & 1023, e >> 22, nb2); };
+    for (int k = wave; k < nb2; k += WAVES) {
+        int cnt = 0;
+        for (int e0 = 0; e0 < n; e0 += 64) cnt += __popcll(__ballot(e0 + lane < n && in_brick(col[e0 + lane], k)));
+        if (lane == 0) start[k] = cnt;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        int run = 0;
+        for (int k0 = 0; k0 < nb2; k0 += 64) {
+            const int v = k0 + lane < nb2 ? start[k0 + lane] : 0;
+            int x = v;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(x, o, 64);
+                if (lane >= o) x += y;
+            }
+            if (k0 + lane < nb2) start[k0 + lane] = run + x - v;
+            run += __shfl(x, 63, 64);
+        }
+        if (lane == 0) {
+            start[nb2] = run;
+            claimed = run > 0 ? atomicAdd(&a.claims[prob * kClaimStride], run) : 0;
+        }
+    }
+    __syncthreads();
+    // (a problem's lists fill the slots of its own atoms, cap_pa each)
+    const int64_t base = int64_t(a0) * a.cap_pa + claimed, brick0 = d.brick_off + int64_t(c) * nb2;
+    for (int k = t; k < nb2; k += kColThreads) {
+        const int64_t first = base + start[k], last = base + start[k + 1];
+        a.offsets[brick0 + k] = int32_t(first < a.capacity ? first : a.capacity);
+        a.ends[brick0 + k] = int32_t(last < a.capacity ? last : a.capacity);
+        if (last > a.capacity) atomicOr(&a.status->bits, 0x4u);
+    }
+    const int k0 = nb2 * wave / WAVES, k1 = nb2 * (wave + 1) / WAVES;
+    uint32_t *st = stage[wave];
+    int64_t slot = base + start[k0];
+    int held = 0;
+    auto write_out = [&](int now) {  // the first `now` <= 64 staged entries
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane < now && slot + lane < a.capacity) {
+            const int v = a0 + int(st[lane] & 4095);
+            const int bc[3] = {b0, b1, int(st[lane] >> 12)};
+            emit_slot(a, d, bc, slot + lane, v, a.info[v]);
+        }
+        slot += now;
+        held -= now;
+        const uint32_t rest = lane < held ? st[64 + lane] : 0u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane < held) st[lane] = rest;
+    };
+    for (int k = k0; k < k1; ++k)
+        for (int e0 = 0; e0 < n; e0 += 64) {
+            const bool hit = e0 + lane < n && in_brick(col[e0 + lane], k);
+            const uint64_t mask = __ballot(hit);
+            if (hit) st[held + __popcll(mask & below)] = (col[e0 + lane] & 4095u) | uint32_t(k) << 12;
+            held += __popcll(mask);
+            if (held >= 64) write_out(64);
+        }
+    if (held > 0) write_out(held);
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_brick_order(SplatArgs a)
+{
+    order_bricks(a, [&](int64_t b) { return a.ends[b] - a.offsets[b]; });
 }
 
 // one wavefront per atom: lanes sum its per-brick partials (slots from the
@@ -570,18 +790,27 @@ __global__ __launch_bounds__(256) void k_adjoint_final(SplatArgs a)
 
 // ------------------------------------------------------------- host side
 
-// The brick counters and cursors are zero on entry: the workspace binding
-// clears them and every binning's sort pass leaves them cleared.
+// The brick counters and cursors of the visits are zero on entry: the workspace
+// binding clears them and every sort pass leaves them cleared.
 hipError_t run_bin(const SplatArgs &a, hipStream_t s)
 {
     const int64_t nbt = a.nbricks_total;
+    int span = 0;
+    for (int p = 0; p < a.nprob; ++p) span = std::max(span, a.atom_off[p + 1] - a.atom_off[p]);
+    // every column reads all atoms of its problem and holds its hits in LDS
+    if (span <= kColAtoms) {
+        const int atom_blocks = std::max(1, (a.natoms + kPrepThreads - 1) / kPrepThreads);
+        const int charge_blocks = a.nprob <= 4 ? a.nprob : (a.nprob + kPrepThreads / 64 - 1) / (kPrepThreads / 64);
+        hipLaunchKernelGGL(k_atom_prep, dim3(atom_blocks + charge_blocks), dim3(kPrepThreads), 0, s, a, atom_blocks);
+        hipLaunchKernelGGL(k_column_gather, dim3(a.ncols), dim3(kColThreads), 4 * size_t(span), s, a);
+        if (a.order) hipLaunchKernelGGL(k_brick_order, dim3(1), dim3(kScanThreads), 0, s, a);
+        return hipGetLastError();
+    }
     const int nw = int((a.natoms + 3) / 4);  // one wavefront per atom
     // the count pass prepares the atoms (AtomInfo): it runs first
     if (a.natoms > 0) hipLaunchKernelGGL(k_brick_visit<0>, dim3(nw), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanThreads), 0, s, a);
     if (a.natoms > 0) hipLaunchKernelGGL(k_brick_visit<1>, dim3(nw), dim3(256), 0, s, a);
-    int span = 0;
-    for (int p = 0; p < a.nprob; ++p) span = std::max(span, a.atom_off[p + 1] - a.atom_off[p]);
     const int words = (span + 31) / 32;
     const int rank_words = words <= kRankWords ? words : 0;
     hipLaunchKernelGGL(k_brick_sort, dim3(int((nbt + 3) / 4)), dim3(256), size_t(rank_words) * 4 * 2 * 4, s, a,

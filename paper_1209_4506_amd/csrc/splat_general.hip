@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void k_splat_general32(SplatArgs a)
     const int lj = lane >> 3, lk = lane & 7;
     const GenSteps st = gen_steps(d);
     const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
+    const int cnt = int(a.ends[b] - off);
     float acc[NS];
 #pragma unroll
     for (int i = 0; i < NS; ++i) acc[i] = 0.0f;
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
     const int prob = brick_prob(a, b);
     const ProbDesc &d = a.desc[prob];
     const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
+    const int cnt = int(a.ends[b] - off);
     const int ways = 4 * split, way = 4 * share + wave;  // entries way, way + ways, ... are this wavefront's
     if (4 * share >= cnt) return;
     const BrickPos p = brick_pos(d, b);
@@ -612,7 +612,7 @@ __global__ __launch_bounds__(64 * kWays) void k_splat_general64(SplatArgs a)
     const int o[3] = {0, 0, kRun * (item % kSeg)};
     if (rows.g0[2] + o[2] >= d.dims[2]) return;
     const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
+    const int cnt = int(a.ends[b] - off);
     const double qc = 0.5 * a.cutoff * a.cutoff;
     double acc[kRun];
 #pragma unroll
@@ -688,7 +688,7 @@ __global__ __launch_bounds__(64 * kWays) void k_adjoint_general64(SplatArgs a, i
     const ProbDesc &d = a.desc[prob];
     const GenRows rows = gen_rows(d, brick_pos(d, b), lane);
     const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
+    const int cnt = int(a.ends[b] - off);
     const int ways = kWays * split, way = kWays * share + wave;
     if (kWays * share >= cnt) return;
     {

@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kMThreads) __attribute__((amdgpu_waves_per_eu(6))) 
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
+    const int cnt = int(a.ends[b] - off);
     const int kk = lane >> 5, col = lane & 31;
     // this lane's A rows: column 32 (2 wave + u) + col, i.e. local
     // i = 4 wave + 2 u + col / 16 and j = col % 16, for u = 0, 1
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kMThreads) __attribute__((amdgpu_waves_per_eu(3))) 
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
+    const int cnt = int(a.ends[b] - off);
     if (cnt == 0) return;
     const int half = lane >> 5, col = lane & 31;
     const LaneAxis la = lane_axis(d, p, lane);

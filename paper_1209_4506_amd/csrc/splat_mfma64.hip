@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kDThreads) void k_splat_mfma64(SplatArgs a)
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
+    const int cnt = int(a.ends[b] - off);
     const LaneAxis64 la = lane_axis64(d, p, lane);
 
     // the accumulators start at the background -Q / Omega
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kDThreads) __attribute__((amdgpu_waves_per_eu(3))) 
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int64_t off = a.offsets[b];
-    const int cnt = int(a.offsets[b + 1] - off);
+    const int cnt = int(a.ends[b] - off);
     if (cnt == 0) return;
     const LaneAxis64 la = lane_axis64(d, p, lane);
 

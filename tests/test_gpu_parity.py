@@ -397,6 +397,48 @@ def test_binding_pairs(H, prec, case):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("natoms", [1, 255, 1025, 4095, 4096])
+@pytest.mark.parametrize("case", ["diagonal", "skew", "batched"])
+def test_binning_forms(H, prec, natoms, case):
+    """The two forms of the binning give the same lists: up to 4,096 atoms a
+    problem (by columns of bricks), and the same atoms followed by atoms
+    without charge, 4,097 in all (by visits).  Density and forces agree to the
+    parity bounds against the oracle; the batched case puts a problem of 30
+    atoms, one of none and another of 30 beside it."""
+    say("case binning forms", prec, natoms, case)
+    rng = np.random.default_rng(natoms)
+    dims = (48, 40, 70)
+    cell = np.diag([12.0, 10.0, 16.0])
+    if case == "skew":
+        cell[1, 0] = 2.0
+    dtype = torch.float32 if prec == "fp32" else torch.float64
+    pos = rng.uniform(-3.0, 20.0, (natoms, 3))
+    Z, sig = rng.uniform(0.5, 2.0, natoms), rng.uniform(0.5, 0.8, natoms)
+    npad = 4097 - natoms
+    pos2 = np.concatenate([pos, rng.uniform(0.0, 10.0, (npad, 3))])
+    Z2, sig2 = np.concatenate([Z, np.zeros(npad)]), np.concatenate([sig, np.full(npad, 0.3)])
+    forms = []
+    for R, q, w, n in ((pos, Z, sig, natoms), (pos2, Z2, sig2, 4097)):
+        cells, shapes, counts = cell, dims, None
+        if case == "batched":
+            cells, shapes, counts = np.stack([cell] * 4), np.array([dims] * 4), [n, 30, 0, 30]
+            R, q, w = (np.concatenate([x, x2[:60]]) for x, x2 in ((R, pos2), (q, 1.0 + sig2), (w, 0.3 + 0.0 * sig2)))
+        plan = H.Plan(cells, shapes, precision=prec, max_atoms=len(q))
+        R, q, w = (torch.as_tensor(x, dtype=torch.float64, device="cuda") for x in (R, q, w))
+        rho = plan.splat(R, q, w, atom_counts=counts)
+        i = torch.arange(rho.numel(), device="cuda", dtype=torch.float64)
+        f = plan.splat_adjoint(R, q, w, torch.cos(i * 1e-3).to(dtype).reshape(rho.shape), atom_counts=counts)
+        torch.cuda.synchronize()
+        assert plan.device_status() == 0
+        f = f.cpu().numpy()
+        forms.append((rho.double().cpu().numpy(), np.concatenate([f[:natoms], f[n:]]), plan.atoms_pairs()))
+    (rho, f, pairs), (rho2, f2, pairs2) = forms
+    assert 0 < pairs < pairs2
+    assert np.abs(rho - rho2).max() <= (1e-13 if prec == "fp64" else 1e-6) * np.abs(rho).max()
+    assert np.abs(f - f2).max() <= (1e-10 if prec == "fp64" else 1e-5) * np.abs(f).max()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_zero_atoms(H, prec):
     """No atoms: the density is zero (no charge, no background), the binding
     is empty, and the adjoint has nothing to write."""
