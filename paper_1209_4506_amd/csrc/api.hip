@@ -506,28 +506,14 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
         if (!d.separable) p->general = true;
         // pass tiles: default radix plan and pencils per workgroup per axis
         for (int x = 0; x < 3; ++x) {
-            // strided axes (a, b): up to 64 pencils side by side; the c axis:
-            // at most 4 pencils, so that a wavefront streams whole rows
-            const int lp = pass_p_log2(p->fp64, N[x], d.ax[x].radix, d.ax[x].nstages, x == 2 ? 4 : 64);
+            int lp, pad;
+            default_tile(p->fp64, x, N[x], d.ax[x].radix, d.ax[x].nstages, lp, pad);
             if (lp < 0) {
                 delete p;
                 return fail(HARTREE_ERR_DIMS, "problem %d: length %d needs more threads per pencil than a workgroup has",
                             q, N[x]);
             }
-            // strided axes: the LDS pitch pad with the fewest modelled bank
-            // conflicts, among those no larger in LDS than a pad of one
-            int pad = 0;
-            if (x < 2) {
-                pad = pass_default_pad(p->fp64, N[x], d.ax[x].radix, d.ax[x].nstages, lp);
-                if (pass_tile_lds(p->fp64, N[x], lp, pad) > pass_tile_lds(p->fp64, N[x], lp, 1)) pad = 1;
-            }
-            const int plan = find_plan(d.ax[x].radix, d.ax[x].nstages);
-            // (no more pencils than set_config accepts)
-            if (plan < 0)
-                p->cfg.push_back({-1, std::min(runtime_default_p_log2(p->fp64, x, N[x]),
-                                               pass_p_log2(p->fp64, N[x], d.ax[x].radix, d.ax[x].nstages, 64)), 0});
-            else
-                p->cfg.push_back({plan, lp, pad});
+            p->cfg.push_back({find_plan(d.ax[x].radix, d.ax[x].nstages), lp, pad});
         }
         // tile counts at one pencil per workgroup bound every choice
         const int64_t rows = int64_t(N[0]) * N[1];

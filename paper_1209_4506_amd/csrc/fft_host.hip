@@ -106,7 +106,8 @@ static double strided_lds_cost(int fp64, int n, const int *radix, int nstages, i
     return ideal > 0.0 ? total / ideal : 1.0;
 }
 
-int pass_default_pad(int fp64, int n, const int *radix, int nstages, int p_log2)
+// the LDS pitch pad with the fewest modelled bank conflicts
+static int modelled_pad(int fp64, int n, const int *radix, int nstages, int p_log2)
 {
     int best = 1;
     double cbest = 0.0;
@@ -164,7 +165,7 @@ void runtime_tile(int fp64, int x, int n, int &p_log2, int &pad)
 //      of the LDS); FP64, two wavefronts per SIMD: n = 135: 8 42, 16 34, 32 39
 //   b  n = 168: 4 15.1, 8 12.6, 16 16.7; n = 625: 2 20.4, 4 18.9, 8 27.5
 //   c  n = 189: 4 16.9, 8 16.4, 16 21.4; n = 280: 2 64, 4 47, 8 57 (past a fourth)
-int runtime_default_p_log2(int fp64, int x, int n)
+static int runtime_default_p_log2(int fp64, int x, int n)
 {
     bool twg;
     int lp = x == 0 ? (fp64 ? 4 : 5) : 3;
@@ -200,6 +201,51 @@ int find_plan(const int *radix, int nstages)
         if (same && nstages <= 4) return i;
     }
     return -1;
+}
+
+// Default pencils per tile of the compiled passes.  A wide strided tile reads
+// long contiguous segments, a narrow one leaves a CU room for more workgroups
+// and cuts a short grid into more of them; 64 KB and more of LDS for a tile
+// (64 pencils up to n = 150, 32 up to 256, 16 up to 512) leaves two per CU.
+// Measured (us; a forward / with E_H, b forward / inverse, c r2c / c2r):
+//   FP32 a  n = 96: 16 10.8 / 9.4, 64 15.6 / 15.9; 180: 16 18.9 / 18.4, 32 21.8 / 21.3; 192: 8 18.8 / 17.8,
+//           16 23.4 / 18.6, 32 28.7 / 28.2; 360: 8 82 / 79, 16 93 / 91; 256: 8 47.9, 16 34.7, 32 42.2 (rows a
+//           power of two apart share few cache sets: the wide tile's longer segments win, so too at 512)
+//   FP32 b  n = 120: 16 8.0 / 10.4, 64 11.6 / 14.1; 192: 8 13.7 / 16.4, 32 19.1 / 20.2; 360: 8 66 / 67, 16 70 / 71
+//   FP64 a  n = 120: 16 17.7, 32 19.7; 150: 16 24.8, 32 33.8; b 150: 16 12.2, 32 19.2; 192: 8 23.3, 16 26.9
+//   c       FP32 n = 128: 4 11.3 / 14.5, 8 9.7 / 10.5; 192: 4 19.9 / 16.6, 8 17.8 / 11.6; 180: 4 19.9 / 16.9,
+//           8 14.8 / 20.5; 288: 4 41 / 42, 8 38 / 54 (half-wavefronts on two rows: no conflict where n is a
+//           multiple of 16); FP64 n = 128: 4 20.9 / 17.7, 8 14.6 / 12.2; 300: 97 / 80, 84 / 85; 360: 142 / 161, 168 / 169
+// FP32 tiles of 16 take a pitch pad of one, so that the kernels are the ones
+// of every other width: those with 16 compiled in round some lengths'
+// butterflies in another order and are 0 to 10 % faster.  Along b from n = 400
+// the padded tile of 8 is 2 to 4 % the faster one (800: 1,127 / 1,095 against
+// 1,153 / 1,118).
+void default_tile(int fp64, int x, int n, const int *radix, int nstages, int &p_log2, int &pad)
+{
+    p_log2 = pass_p_log2(fp64, n, radix, nstages, 64);
+    pad = 0;
+    if (p_log2 < 0) return;
+    if (find_plan(radix, nstages) < 0) {  // (no more pencils than set_config accepts)
+        p_log2 = std::min(p_log2, runtime_default_p_log2(fp64, x, n));
+        return;
+    }
+    if (x == 2) {
+        const bool eight = fp64 ? n <= 300 : n <= 160 || (n <= 256 && n % 16 == 0);
+        p_log2 = std::min(p_log2, eight ? 3 : 2);
+        return;
+    }
+    const bool pow2 = (n & (n - 1)) == 0;
+    if (fp64) {
+        p_log2 = std::min(p_log2, x == 0 || n <= 160 ? 4 : 3);
+        // (among those no larger in LDS than a pad of one)
+        pad = modelled_pad(fp64, n, radix, nstages, p_log2);
+        if (pass_tile_lds(fp64, n, p_log2, pad) > pass_tile_lds(fp64, n, p_log2, 1)) pad = 1;
+        return;
+    }
+    const bool wide = n <= 180 || pow2;
+    p_log2 = std::min(p_log2, wide ? 4 : 3);
+    pad = (p_log2 == 4 && n < 512) || (x == 1 && p_log2 == 3 && n >= 400) ? 1 : 0;
 }
 
 hipError_t run_pass(int fp64, PassKind kind, int plan, int p_log2, int pad, int maxn, int grid, hipStream_t s,

@@ -75,13 +75,13 @@ inline const int *multi_plans(int x) { return x == 2 ? kMultiPlansC : kMultiPlan
 int pass_p_log2(int fp64, int n, const int *radix, int nstages, int max_p);
 int pass_min_tpp(int fp64, int n, const int *radix, int nstages);
 size_t pass_tile_lds(int fp64, int n, int p_log2, int pad);
-int pass_default_pad(int fp64, int n, const int *radix, int nstages, int p_log2);
 // LDS of a run-time radix tile along axis x (two copies of the tile and, unless
-// twg, the twiddle table), the tile it actually takes when the requested one
-// does not fit, and the default tile of a length without a compiled plan
+// twg, the twiddle table), and the tile it actually takes when the requested
+// one does not fit
 size_t runtime_lds(int fp64, int x, int n, int p_log2, int pad, bool &twg);
 void runtime_tile(int fp64, int x, int n, int &p_log2, int &pad);
-int runtime_default_p_log2(int fp64, int x, int n);
+// the tile of a pass as plans are created: pencils (log2; negative: none fits) and pitch pad
+void default_tile(int fp64, int x, int n, const int *radix, int nstages, int &p_log2, int &pad);
 int find_plan(const int *radix, int nstages);
 int plan_table_size();
 int plan_table_row(int id, int *radix);  // fills radix[4], returns the stage count

@@ -595,6 +595,43 @@ def test_every_compiled_plan(H, oracle_mod, prec, n):
     assert checked >= 12
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [32, 160, 180, 192, 256, 288, 300, 320, 400, 512, 600])
+def test_default_tiles(H, prec, n):
+    """The tile a plan is created with against the widest tile along a and b
+    and four pencils along c, on each axis at the lengths where the choice
+    turns: the tile shape moves no rounding of the FP32 potential and
+    gradient, and E_H only by the order of its sum over tiles (double)."""
+    say("case default tiles", prec, n)
+    for x in range(3):
+        dims = [12, 10, 14]
+        dims[x] = n
+        plan = H.Plan(CELLS["triclinic"], tuple(dims), precision=prec, max_atoms=1)
+        rho = to_dev(inputs.random_grid(tuple(dims), 51 + x).astype(np.float32), plan.dtype)
+        ge = torch.tensor([0.3], dtype=torch.float64)
+        out = []
+        for wide in (False, True):
+            cfg = plan.get_config()
+            lps = range(2 if x == 2 else 6, -1, -1) if wide else [cfg[0, x, 1]]
+            for lp in lps:
+                cfg[0, x, 1:] = (lp, 0 if wide else cfg[0, x, 2])
+                try:
+                    plan.set_config(cfg)
+                    break
+                except H.HartreeError:
+                    continue
+            V, E = plan.solve(rho)
+            G = plan.backward(grad_v=rho, grad_e=ge, rho=rho)
+            torch.cuda.synchronize()
+            out.append((V.double(), G.double(), float(E[0])))
+        (V, G, E), (V2, G2, E2) = out
+        for got, want in ((V, V2), (G, G2)):
+            if prec == "fp32":
+                assert torch.equal(got, want), (x, n)
+            assert (got - want).abs().max() <= 1e-14 * want.abs().max(), (x, n)
+        assert abs(E - E2) <= 1e-14 * abs(E2), (x, n)
+
+
 # lengths without a compiled plan: one to four stages, every radix first and
 # last, with and without radix 16, up to the longest (in FP64 the longest read
 # their twiddles from global memory)
