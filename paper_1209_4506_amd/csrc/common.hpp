@@ -130,16 +130,19 @@ struct SlotAtom {
 
 // The same for the FP64 splat kernels, in double precision: the unwrapped
 // offset r has grid index lo + r and displacement (lo + r) h - X.
-struct SlotAtom64 {
-    double X[3];     // the wrapped position per axis
+struct SlotAxis64 {
+    double X;        // the wrapped position
+    int32_t lo;      // window start (unwrapped grid index)
+    int32_t r0;      // offset of the brick's first point from the window start, mod n
+    int32_t wl;      // window width in points; 0 for an atom that touches nothing
+    int32_t pad;
+};
+struct alignas(16) SlotAtom64 {
+    SlotAxis64 ax[3];
     double inv2s2;   // 1 / (2 sigma^2): the 1-D factor is exp(-d^2 inv2s2)
     double w;        // Z (2 pi sigma^2)^(-3/2)
-    int32_t lo[3];   // window start per axis (unwrapped grid index)
-    int32_t r0[3];   // offset of the brick's first point from the window start, mod n
-    int32_t wl[3];   // window width in points; 0 for an atom that touches nothing
     int32_t atom;    // the atom's index ...
     int32_t touch;   // ... and this brick's place in its enumeration of touched bricks
-    int32_t pad;
 };
 
 struct DeviceStatus {

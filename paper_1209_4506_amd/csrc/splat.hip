@@ -403,16 +403,16 @@ __device__ __forceinline__ void emit_slot(const SplatArgs &a, const ProbDesc &d,
         // the atom relative to this brick, for the FP64 splat kernels
         SlotAtom64 r;
         for (int x = 0; x < 3; ++x) {
-            r.X[x] = in.X[x];
-            r.lo[x] = in.lo[x];
-            r.r0[x] = wrapi(bc[x] * d.bsz[x] - in.lo[x], d.dims[x]);
-            r.wl[x] = in.hi[x] >= in.lo[x] ? in.hi[x] - in.lo[x] + 1 : 0;
+            r.ax[x].X = in.X[x];
+            r.ax[x].lo = in.lo[x];
+            r.ax[x].r0 = wrapi(bc[x] * d.bsz[x] - in.lo[x], d.dims[x]);
+            r.ax[x].pad = 0;
+            r.ax[x].wl = in.hi[x] >= in.lo[x] ? in.hi[x] - in.lo[x] + 1 : 0;
         }
         r.inv2s2 = in.inv2s2;
         r.w = in.w;
         r.atom = v;
         r.touch = ti;
-        r.pad = 0;
         a.rec64[slot] = r;
     }
     if (a.rec) {

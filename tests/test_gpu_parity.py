@@ -438,6 +438,31 @@ def test_binning_forms(H, prec, natoms, case):
     assert np.abs(f - f2).max() <= (1e-10 if prec == "fp64" else 1e-5) * np.abs(f).max()
 
 
+@pytest.mark.parametrize("natoms", [3, 64, 65, 130, 300])
+@pytest.mark.parametrize("dims", [(32, 32, 64), (20, 18, 40)])
+def test_partly_covered_bricks(H, oracle_mod, natoms, dims):
+    """FP64 atoms whose windows cover little of their bricks beside atoms that
+    cover all of them, in lists around the sizes that are staged and ordered
+    together (64 and 128): density and forces against the oracle at the
+    parity bounds of the other cases."""
+    say("case partly covered bricks", natoms, dims)
+    rng = np.random.default_rng(natoms)
+    L = 0.3 * np.array(dims)
+    pos = rng.uniform(0.0, 1.0, (natoms, 3)) * L
+    Z, sig = rng.uniform(0.5, 2.0, natoms), np.where(np.arange(natoms) % 3 == 0, 0.6, 0.25)
+    plan = H.Plan(np.diag(L), dims, precision="fp64", max_atoms=natoms)
+    R, q, w = (torch.as_tensor(x, dtype=torch.float64, device="cuda") for x in (pos, Z, sig))
+    cell9 = np.diag(L).reshape(9)
+    rho = plan.splat(R, q, w).cpu().numpy()
+    ref = oracle_mod.splat(cell9, dims, pos, Z, sig)
+    assert np.abs(rho - ref).max() <= 1e-13 * np.abs(ref).max()
+    g = oracle_mod.poisson(cell9, ref)[0]
+    f = plan.splat_adjoint(R, q, w, to_dev(g, plan.dtype)).cpu().numpy()
+    want = oracle_mod.splat_adjoint(cell9, pos, Z, sig, g)
+    assert np.abs(f - want).max() <= 1e-10 * np.abs(want).max()
+    assert plan.device_status() == 0
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_zero_atoms(H, prec):
     """No atoms: the density is zero (no charge, no background), the binding
