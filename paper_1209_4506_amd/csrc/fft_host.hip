@@ -212,7 +212,9 @@ int find_plan(const int *radix, int nstages)
 //           16 23.4 / 18.6, 32 28.7 / 28.2; 360: 8 82 / 79, 16 93 / 91; 256: 8 47.9, 16 34.7, 32 42.2 (rows a
 //           power of two apart share few cache sets: the wide tile's longer segments win, so too at 512)
 //   FP32 b  n = 120: 16 8.0 / 10.4, 64 11.6 / 14.1; 192: 8 13.7 / 16.4, 32 19.1 / 20.2; 360: 8 66 / 67, 16 70 / 71
-//   FP64 a  n = 120: 16 17.7, 32 19.7; 150: 16 24.8, 32 33.8; b 150: 16 12.2, 32 19.2; 192: 8 23.3, 16 26.9
+//   FP64 a  n = 120: 8 16.1, 16 18.1, 32 19.6; 192: 4 32.6, 8 29.4, 16 38.4; 300: 4 98, 8 90; 420: 4 316, 8 379 (the
+//           kernels of 4 and 8 without pad are compiled for them); 256: 8 74, 16 60; 512: 4 572, 8 535
+//   FP64 b  n = 150: 16 12.2, 32 19.2; 192: 8 23.3, 16 26.9
 //   c       FP32 n = 128: 4 11.3 / 14.5, 8 9.7 / 10.5; 192: 4 19.9 / 16.6, 8 17.8 / 11.6; 180: 4 19.9 / 16.9,
 //           8 14.8 / 20.5; 288: 4 41 / 42, 8 38 / 54 (half-wavefronts on two rows: no conflict where n is a
 //           multiple of 16); FP64 n = 128: 4 20.9 / 17.7, 8 14.6 / 12.2; 300: 97 / 80, 84 / 85; 360: 142 / 161, 168 / 169
@@ -237,6 +239,10 @@ void default_tile(int fp64, int x, int n, const int *radix, int nstages, int &p_
     }
     const bool pow2 = (n & (n - 1)) == 0;
     if (fp64) {
+        if (x == 0 && n != 256) {
+            p_log2 = std::min(p_log2, n <= 320 || pow2 ? 3 : 2);
+            return;
+        }
         p_log2 = std::min(p_log2, x == 0 || n <= 160 ? 4 : 3);
         // (among those no larger in LDS than a pad of one)
         pad = modelled_pad(fp64, n, radix, nstages, p_log2);
