@@ -11,13 +11,19 @@ hipError_t launch_one(int grid, size_t lds, hipStream_t s, const PassArgs &a)
 {
     return launch_pass(k_fft_b<float, R0, R1, R2, R3, CP>, grid, lds, s, a);
 }
+template <int R0, int R1, int R2, int R3>
+hipError_t launch_fixed8(int grid, size_t lds, hipStream_t s, const PassArgs &a)
+{
+    constexpr int NT = threads8<float>(1, plan_length(R0, R1, R2, R3));
+    return launch_pass(k_fft_b<float, R0, R1, R2, R3, 8, NT>, grid, lds, s, a, NT);
+}
 #define HARTREE_ENTRY(R0, R1, R2, R3) &launch_one<R0, R1, R2, R3, 0>,
 const PassLaunchFn kTable[] = {HARTREE_PLANS(HARTREE_ENTRY)};
 #undef HARTREE_ENTRY
 #define HARTREE_ENTRY(R0, R1, R2, R3) &launch_one<R0, R1, R2, R3, 4>,
 const PassLaunchFn kFixed4[] = {HARTREE_PLANS(HARTREE_ENTRY)};
 #undef HARTREE_ENTRY
-#define HARTREE_ENTRY(R0, R1, R2, R3) &launch_one<R0, R1, R2, R3, 8>,
+#define HARTREE_ENTRY(R0, R1, R2, R3) &launch_fixed8<R0, R1, R2, R3>,
 const PassLaunchFn kFixed8[] = {HARTREE_PLANS(HARTREE_ENTRY)};
 #undef HARTREE_ENTRY
 #define HARTREE_ENTRY(R0, R1, R2, R3) &launch_one<R0, R1, R2, R3, 16>,

@@ -220,9 +220,7 @@ int find_plan(const int *radix, int nstages)
 //           multiple of 16); FP64 n = 128: 4 20.9 / 17.7, 8 14.6 / 12.2; 300: 97 / 80, 84 / 85; 360: 142 / 161, 168 / 169
 // FP32 tiles of 16 take a pitch pad of one, so that the kernels are the ones
 // of every other width: those with 16 compiled in round some lengths'
-// butterflies in another order and are 0 to 10 % faster.  Along b from n = 400
-// the padded tile of 8 is 2 to 4 % the faster one (800: 1,127 / 1,095 against
-// 1,153 / 1,118).
+// butterflies in another order and are 0 to 10 % faster.
 void default_tile(int fp64, int x, int n, const int *radix, int nstages, int &p_log2, int &pad)
 {
     p_log2 = pass_p_log2(fp64, n, radix, nstages, 64);
@@ -251,7 +249,7 @@ void default_tile(int fp64, int x, int n, const int *radix, int nstages, int &p_
     }
     const bool wide = n <= 180 || pow2;
     p_log2 = std::min(p_log2, wide ? 4 : 3);
-    pad = (p_log2 == 4 && n < 512) || (x == 1 && p_log2 == 3 && n >= 400) ? 1 : 0;
+    pad = p_log2 == 4 && n < 512 ? 1 : 0;
 }
 
 hipError_t run_pass(int fp64, PassKind kind, int plan, int p_log2, int pad, int maxn, int grid, hipStream_t s,

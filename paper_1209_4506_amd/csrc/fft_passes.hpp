@@ -416,10 +416,9 @@ __global__ __launch_bounds__(256) void k_c2r(PassArgs a)
 // stage reads the tile from the spectrum and the last writes it back.
 // CP > 0: tiles of exactly CP pencils with no pitch pad, compiled in (as for
 // the a pass).
-template <typename T, int R0, int R1, int R2, int R3, int CP>
+template <typename T, int R0, int R1, int R2, int R3, int CP, int NT = kPassThreads>
 __device__ __forceinline__ void fft_b_tile(const PassArgs &a, int prob, int tile)
 {
-    constexpr int NT = kPassThreads;
     const int P = CP > 0 ? CP : 1 << a.p_log2;
     const int TPP = NT / P;
     const int PP = CP > 0 ? CP : P + a.pad;
@@ -443,12 +442,12 @@ __device__ __forceinline__ void fft_b_tile(const PassArgs &a, int prob, int tile
     fft_static<T, R0, R1, R2, R3>(gp, gp, lp, tw, d.ax[1], tip, TPP);
 }
 
-template <typename T, int R0, int R1, int R2, int R3, int CP = 0>
-__global__ __launch_bounds__(256) void k_fft_b(PassArgs a)
+template <typename T, int R0, int R1, int R2, int R3, int CP = 0, int NT = kPassThreads>
+__global__ __launch_bounds__(NT) void k_fft_b(PassArgs a)
 {
     int prob, tile;
     find_item(a.tl, xcd_remap(blockIdx.x, gridDim.x), prob, tile);
-    fft_b_tile<T, R0, R1, R2, R3, CP>(a, prob, tile);
+    fft_b_tile<T, R0, R1, R2, R3, CP, NT>(a, prob, tile);
 }
 
 // ---------------------------------------------------------------- P3
@@ -618,10 +617,9 @@ struct KernelMultiply {
 // it only for that shape), so the tile pitch and the threads per pencil are
 // compile-time constants: LDS offsets become immediates and the per-stage
 // bounds checks fold away.
-template <typename T, int R0, int R1, int R2, int R3, int CP>
+template <typename T, int R0, int R1, int R2, int R3, int CP, int NT = kPassThreads>
 __device__ __forceinline__ void fft_a_tile(const PassArgs &a, int prob, int tile)
 {
-    constexpr int NT = kPassThreads;
     const int P = CP > 0 ? CP : 1 << a.p_log2;
     const int TPP = NT / P;
     const int PP = CP > 0 ? CP : P + a.pad;
@@ -676,12 +674,12 @@ __device__ __forceinline__ void fft_a_tile(const PassArgs &a, int prob, int tile
     }
 }
 
-template <typename T, int R0, int R1, int R2, int R3, int CP = 0>
-__global__ __launch_bounds__(256) void k_fft_a(PassArgs a)
+template <typename T, int R0, int R1, int R2, int R3, int CP = 0, int NT = kPassThreads>
+__global__ __launch_bounds__(NT) void k_fft_a(PassArgs a)
 {
     int prob, tile;
     find_item(a.tl, xcd_remap(blockIdx.x, gridDim.x), prob, tile);
-    fft_a_tile<T, R0, R1, R2, R3, CP>(a, prob, tile);
+    fft_a_tile<T, R0, R1, R2, R3, CP, NT>(a, prob, tile);
 }
 
 // ----------------------------------------------------- multi-plan launches
@@ -810,20 +808,40 @@ inline hipError_t lds_opt_in(const void *kern, size_t lds)
 }
 
 template <typename F>
-static hipError_t launch_pass(F kern, int grid, size_t lds, hipStream_t s, const PassArgs &a)
+static hipError_t launch_pass(F kern, int grid, size_t lds, hipStream_t s, const PassArgs &a,
+                              int threads = kPassThreads)
 {
     if (grid <= 0) return hipSuccess;
     if (lds > 65536) {
         hipError_t e = lds_opt_in(reinterpret_cast<const void *>(kern), lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, s, a);
     return hipGetLastError();
+}
+
+// Threads of the strided kernels with 8 pencils compiled in, by length.  A long
+// tile's LDS leaves a CU two or three workgroups, and 512 threads give each of
+// them twice the wavefronts, with half the butterflies and registers to a
+// thread.  Measured (us, 256 / 512 threads, n^3):
+//   FP32 b  300 40.6 / 43.3, 400 102 / 88, 600 468 / 436, 800 1,151 / 1,011, 1024 2,377 / 2,059
+//   FP32 a  640 549 / 668, 720 1,048 / 912, 960 2,689 / 2,293, 1024 2,731 / 2,517 (below 720 the
+//           pass is bound by its work between the barriers, which more wavefronts only share)
+//           (360 as 9 x 8 x 5 75 / 68, but as 12 x 5 x 6, which tuned plans take, 60 / 61: kept at 256)
+//   FP64 b  180 21.8 / 20.5, 256 44.5 / 54.8, 360 174 / 168, 512 458 / 425
+// (512 in FP32 stays at 256 threads: there the other work split rounds its
+// butterflies in another order.)
+template <typename T>
+constexpr int threads8(int x, int n)
+{
+    if (sizeof(T) == 8) return x == 1 && n >= 180 && n != 256 ? 512 : kPassThreads;
+    return n >= (x == 0 ? 720 : 384) && n != 512 ? 512 : kPassThreads;
 }
 
 // Strided tiles of compiled width keep each thread's offset from the tile's
 // first pencil, tip * stride + column, as a 32-bit byte offset: true when that
-// fits for every problem of the launch (the largest stride, tpp - 1 tips).
+// fits for every problem of the launch (the largest stride, tpp - 1 tips; with
+// 512 threads twice the tips, at lengths that leave no such strides).
 template <typename T>
 inline bool lane_offsets_fit(const PassArgs &a)
 {
