@@ -1458,8 +1458,13 @@ hartree_status hartree_plan_tune(hartree_plan plan, void *grid, int32_t reps, vo
                         if (choice_radices(plan, x, n, id, lp, pad, r) &&
                             (id >= 0 || find_plan(r.data(), int(r.size())) < 0))
                             cand.push_back({id, lp, pad});
+            struct Timed {
+                int id;
+                float ms;
+                std::vector<int32_t> cfg;
+            };
+            std::vector<Timed> fastest;  // of each radix plan, in the order of their ids
             float best = 0.0f;
-            std::vector<int32_t> best_cfg = cfg;
             for (const auto &c : cand) {
                 std::vector<int32_t> trial = cfg;
                 for (int q = 0; q < plan->nprob; ++q)
@@ -1473,11 +1478,31 @@ hartree_status hartree_plan_tune(hartree_plan plan, void *grid, int32_t reps, vo
                     if (result != HARTREE_OK) break;
                     continue;
                 }
-                if (best == 0.0f || ms < best) {
-                    best = ms;
-                    best_cfg = trial;
-                }
+                if (fastest.empty() || fastest.back().id != c.id) fastest.push_back({c.id, ms, trial});
+                else if (ms < fastest.back().ms) fastest.back() = {c.id, ms, trial};
+                if (best == 0.0f || ms < best) best = ms;
             }
+            // Radix plans of one length round differently, and two are often
+            // closer than a timing repeats (360 along a: 152.3 and 153.6 us,
+            // timings 3 % apart).  So that tuning again gives the same values,
+            // those near the least time are timed four times more, in turn, and
+            // of the ones then within 1 % of it the first is taken.
+            const float near = 1.03f * best;
+            fastest.erase(std::remove_if(fastest.begin(), fastest.end(), [&](const Timed &t) { return t.ms > near; }),
+                          fastest.end());
+            for (int round = 0; round < 4 && fastest.size() > 1 && result == HARTREE_OK; ++round)
+                for (auto &t : fastest) {
+                    float ms = 0.0f;
+                    if (!time_axis(x, t.cfg, ms)) break;
+                    t.ms = std::min(t.ms, ms);
+                    best = std::min(best, ms);
+                }
+            std::vector<int32_t> best_cfg = cfg;
+            for (const auto &t : fastest)
+                if (t.ms <= 1.01f * best) {
+                    best_cfg = t.cfg;
+                    break;
+                }
             if (result != HARTREE_OK) break;
             cfg = best_cfg;
         }
