@@ -1482,12 +1482,12 @@ hartree_status hartree_plan_tune(hartree_plan plan, void *grid, int32_t reps, vo
                 else if (ms < fastest.back().ms) fastest.back() = {c.id, ms, trial};
                 if (best == 0.0f || ms < best) best = ms;
             }
-            // Radix plans of one length round differently, and two are often
-            // closer than a timing repeats (360 along a: 152.3 and 153.6 us,
-            // timings 3 % apart).  So that tuning again gives the same values,
-            // those near the least time are timed four times more, in turn, and
-            // of the ones then within 1 % of it the first is taken.
-            const float near = 1.03f * best;
+            // Radix plans of one length round differently in FP32, and two are
+            // often closer than a timing repeats (360 along a: 152.3 and 153.6
+            // us, timings 3 % apart).  So that tuning again gives the same
+            // values, those near the least time are timed four times more, in
+            // turn, and of the ones then within 1 % of it the first is taken.
+            const float near = (plan->fp64 ? 1.0f : 1.03f) * best;
             fastest.erase(std::remove_if(fastest.begin(), fastest.end(), [&](const Timed &t) { return t.ms > near; }),
                           fastest.end());
             for (int round = 0; round < 4 && fastest.size() > 1 && result == HARTREE_OK; ++round)
@@ -1499,7 +1499,7 @@ hartree_status hartree_plan_tune(hartree_plan plan, void *grid, int32_t reps, vo
                 }
             std::vector<int32_t> best_cfg = cfg;
             for (const auto &t : fastest)
-                if (t.ms <= 1.01f * best) {
+                if (t.ms <= (plan->fp64 ? 1.0f : 1.01f) * best) {
                     best_cfg = t.cfg;
                     break;
                 }
