@@ -120,4 +120,38 @@ __device__ __forceinline__ float expT<float>(float x) { return expf(x); }
 template <>
 __device__ __forceinline__ double expT<double>(double x) { return exp(x); }
 
+// exp(x): x = n ln 2 + r, |r| <= ln 2 / 2, exp(r) by its Taylor series to
+// r^13 / 13! (the next term is 4e-18).  Without the library's range checks and
+// branches: 2^n underflows to 0 and overflows by itself.  The coefficients are
+// read from memory, so that they stay in scalar registers; ln 2 is split in
+// 2^-40 floor(2^40 ln 2 + 1/2) and the rest, so that n times the first is exact.
+static __constant__ double kExp[17] = {
+    1.0 / 0.69314718055994530942, -762123384786.0 / 1099511627776.0, 1.7239444525614835e-13,
+    1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0,
+    1.0 / 5040.0, 1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0, 0.5, 1.0, 1.0};
+__device__ __forceinline__ double exp64(double x)
+{
+    const double n = __builtin_rint(x * kExp[0]);
+    const double r = __builtin_fma(n, kExp[2], __builtin_fma(n, kExp[1], x));
+    double e = kExp[3];
+#pragma unroll
+    for (int k = 4; k < 17; ++k) e = __builtin_fma(e, r, kExp[k]);
+    return __builtin_ldexp(e, int(n));
+}
+// exp(x) and exp(-x): one reduction, and the series' even and odd terms once
+__device__ __forceinline__ void exp64_pair(double x, double &plus, double &minus)
+{
+    const double n = __builtin_rint(x * kExp[0]);
+    const double r = __builtin_fma(n, kExp[2], __builtin_fma(n, kExp[1], x));
+    const double r2 = r * r;
+    double odd = kExp[3], even = kExp[4];
+#pragma unroll
+    for (int k = 5; k < 17; k += 2) {
+        odd = __builtin_fma(odd, r2, kExp[k]);
+        even = __builtin_fma(even, r2, kExp[k + 1]);
+    }
+    plus = __builtin_ldexp(__builtin_fma(r, odd, even), int(n));
+    minus = __builtin_ldexp(__builtin_fma(-r, odd, even), -int(n));
+}
+
 }  // namespace hartree

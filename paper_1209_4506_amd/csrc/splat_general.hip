@@ -498,7 +498,8 @@ __device__ __forceinline__ GenRows gen_rows(const ProbDesc &d, const BrickPos &p
 
 // The run's eight exponentials, t_k = tm + k c for k = -4 .. 3: with x =
 // exp(-2 tm c), exp(-(s + t_k^2)) = exp(-(s + tm^2)) x^k exp(-c^2 k^2), three
-// exponentials and a few products instead of eight exponentials.  The error is
+// exponentials (x^-1 = exp(2 tm c) and x from one reduction) and a few products
+// instead of eight exponentials.  The error is
 // that of the exponents' terms, eps (s + tm^2 + |2 tm c k| + c^2 k^2), a few
 // ulps while 4 c is about a width or less; taken only for c <= 0.5 (grid
 // spacing up to 0.7 sigma), otherwise the points are evaluated one by one
@@ -513,10 +514,10 @@ __device__ __forceinline__ GenRun gen_run(double c, double qc)
     r.c = c;
     const double reach = sqrt(qc) + 4.0 * c;  // largest |tm| of a run inside the sphere
     r.direct = !(c <= 0.5 && qc + reach * reach < 600.0 && 8.0 * reach * c < 600.0);
-    r.k1 = exp(-c * c);
-    r.k2 = exp(-4.0 * c * c);
-    r.k3 = exp(-9.0 * c * c);
-    r.k4 = exp(-16.0 * c * c);
+    r.k1 = exp64(-c * c);
+    r.k2 = exp64(-4.0 * c * c);
+    r.k3 = exp64(-9.0 * c * c);
+    r.k4 = exp64(-16.0 * c * c);
     return r;
 }
 __device__ __forceinline__ GenRun lane_run(const GenRun &r, int q)
@@ -541,11 +542,12 @@ __device__ __forceinline__ void gen_exps(const GenRun &r, double s, double tm, d
     }
     if (r.direct) {
 #pragma unroll
-        for (int j = 0; j < kRun; ++j) e[j] = exp(-fma(t[j], t[j], s));
+        for (int j = 0; j < kRun; ++j) e[j] = exp64(-fma(t[j], t[j], s));
         return;
     }
-    const double A = exp(-fma(tm, tm, s));
-    const double x = exp(-2.0 * tm * r.c), y = exp(2.0 * tm * r.c);
+    const double A = exp64(-fma(tm, tm, s));
+    double x, y;
+    exp64_pair(-2.0 * tm * r.c, x, y);
     const double x2 = x * x, y2 = y * y;
     const double A1 = A * r.k1, A2 = A * r.k2, A3 = A * r.k3;
     e[0] = (A * r.k4) * (y2 * y2);
@@ -768,8 +770,10 @@ hipError_t run_gather_general(const SplatArgs &a, hipStream_t s)
 hipError_t run_adjoint_general(const SplatArgs &a, hipStream_t s)
 {
     const int nb = int(a.nbricks_total);
-    const int split = nb < kFewBricks ? 8 : 2;
+    int split = nb < kFewBricks ? 8 : 2;
     if (a.fp64) {
+        // (72 x 80 x 90, 270 bricks of 8 x 8 x 32: 1 105 us, 2 79, 4 74, 6 72, 8 76)
+        if (nb >= kFewBricks && nb < 4 * kFewBricks) split = 4;
         hipLaunchKernelGGL(k_adjoint_general64, dim3(nb * split), dim3(64 * kWays), 0, s, a, split);
     } else {
         if (a.many)

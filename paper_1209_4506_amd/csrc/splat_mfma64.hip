@@ -66,25 +66,7 @@ __device__ __forceinline__ LaneAxis64 lane_axis64(const ProbDesc &d, const Brick
     return la;
 }
 
-// exp(x) for x <= 0: x = n ln 2 + r, |r| <= ln 2 / 2, exp(r) by its Taylor
-// series to r^13 / 13! (the next term is 4e-18).  Without the library's range
-// checks, which x <= 0 does not need: 2^n underflows to 0 by itself.  The
-// coefficients are read from memory, so that they stay in scalar registers;
-// ln 2 is split in 2^-40 floor(2^40 ln 2 + 1/2) and the rest, n times the first is exact.
-__constant__ double kExp[17] = {1.0 / 0.69314718055994530942, -762123384786.0 / 1099511627776.0, 1.7239444525614835e-13,
-                                1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0,
-                                1.0 / 362880.0, 1.0 / 40320.0, 1.0 / 5040.0, 1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0,
-                                1.0 / 6.0, 0.5, 1.0, 1.0};
-constexpr double kExpZero = -2000.0;  // exp_neg gives 0
-__device__ __forceinline__ double exp_neg(double x)
-{
-    const double n = __builtin_rint(x * kExp[0]);
-    const double r = __builtin_fma(n, kExp[2], __builtin_fma(n, kExp[1], x));
-    double e = kExp[3];
-#pragma unroll
-    for (int k = 4; k < 17; ++k) e = __builtin_fma(e, r, kExp[k]);
-    return __builtin_ldexp(e, int(n));
-}
+constexpr double kExpZero = -2000.0;  // exp64 gives 0
 
 struct Entry64 {
     double g, gd;  // factor and displacement-weighted factor
@@ -103,7 +85,7 @@ __device__ __forceinline__ Entry64 entry64(const LaneAxis64 &la, const SlotAtom6
     r = r >= la.n ? r - la.n : r;
     const double d = double(ax.lo + r) * la.h - ax.X;
     // (chosen before the exponential, not after, so that it has no branch)
-    const double e = exp_neg((r | la.beyond) < ax.wl ? -(d * d) * at.inv2s2 : kExpZero);
+    const double e = exp64((r | la.beyond) < ax.wl ? -(d * d) * at.inv2s2 : kExpZero);
     return Entry64{e, e * d, ((r + la.n) | la.beyond) < ax.wl};
 }
 
@@ -114,7 +96,7 @@ __device__ __forceinline__ void more_images64(const LaneAxis64 &la, const SlotAt
     r = r >= la.n ? r - la.n : r;
     for (r += la.n; (r | la.beyond) < ax.wl; r += la.n) {
         const double d = double(ax.lo + r) * la.h - ax.X;
-        const double e = exp_neg(-(d * d) * at.inv2s2);
+        const double e = exp64(-(d * d) * at.inv2s2);
         gs += e;
         gds += e * d;
     }
