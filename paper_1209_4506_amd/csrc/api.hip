@@ -669,16 +669,30 @@ int kernel_id(PassKind kind)
     }
 }
 
+bool under_capture(hipStream_t s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return c != hipStreamCaptureStatusNone;
+}
+
 // The launch groups of one pass.  With side streams (batched plans) the
 // groups are dealt, largest first, to the least-loaded of the caller's stream
 // and the side streams, forked after the work already on `s` and joined back
 // before the pass returns; results do not depend on the dealing (disjoint
-// problems, fixed per-problem sums).
+// problems, fixed per-problem sums).  Under capture they run in order on s: a
+// captured step of six problems, forked in four and five groups to a pass,
+// ended its process with a segmentation fault in host code, as another had
+// inside the runtime's recording of the graph, and no fault of these calls was
+// found.  (hartree_solve_backward's two chains are two branches either way.)
 hipError_t run_group(hartree_plan p, const std::vector<Launch> &groups, PassKind kind, PassArgs a, hipStream_t s)
 {
     return timed(p, kernel_id(kind), s, [&]() -> hipError_t {
         const int ng = int(groups.size());
-        const int nside = (ng > 1 && p->side_ready) ? std::min(ng - 1, int(hartree_plan_s::kSide)) : 0;
+        const int nside = (ng > 1 && p->side_ready && !under_capture(s)) ? std::min(ng - 1, int(hartree_plan_s::kSide)) : 0;
         if (nside == 0) {
             for (const Launch &l : groups) {
                 a.tl = l.tl;
@@ -1017,13 +1031,14 @@ hartree_status hartree_solve_backward(hartree_plan plan, const void *rho, void *
     b.grad_e = grad_e;
     b.out = grad_rho;
     // The chains run side by side when their two spectra fit the last-level
-    // cache together, and every pass is one launch group (single plans;
-    // batched plans whose problems all take multi-plan launches), so that the
-    // backward chain forks no side streams of its own.  Otherwise, or without
+    // cache together, and neither forks side streams of its own: every pass is
+    // one launch group (single plans; batched plans whose problems all take
+    // multi-plan launches) or the groups run in order (capture).  Otherwise, or without
     // the plan's streams, in order on the caller's stream: a spectrum that
     // fits the cache alone stays there from one pass to the next, which two
     // chains side by side would give up.
-    const bool single_groups = plan->lr2c.size() == 1 && plan->lb.size() == 1 && plan->la.size() == 1;
+    const bool single_groups =
+        (plan->lr2c.size() == 1 && plan->lb.size() == 1 && plan->la.size() == 1) || under_capture(s);
     const size_t spec_bytes = size_t(plan->spec_count) * (plan->fp64 ? 16 : 8);
     if (!plan->side_ready || !single_groups || 2 * spec_bytes > kOverlapCacheBytes) {
         // in order, on the one spectrum (the cache still holds it)
