@@ -565,6 +565,9 @@ __global__ __launch_bounds__(256) void k_brick_sort(SplatArgs a, int rank_words)
 // address take 10 ns each (24 problems, 972 columns: 27 us against 19).
 // 32^3, 8 atoms: 22 -> 13 us; 180^3, 512 atoms: 30 -> 17; 24 batched problems: 68 ->
 // 36; 360^3, 4,096 atoms: 50 -> 37 (with about 5 us of event time in each).
+// Taken over chunks of 4,096 it no longer pays, each column testing all atoms
+// twice: 420 x 420 x 210, 16,384 atoms, 70 us against 69 by visits; 1024^3,
+// 32,768 atoms, 421 against 323.
 constexpr int kColAtoms = 4096;
 constexpr int kColThreads = 256;  // 64, 128 and 512 threads a column are within 15 % of it or slower
 
