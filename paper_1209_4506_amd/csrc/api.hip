@@ -1030,17 +1030,20 @@ hartree_status hartree_solve_backward(hartree_plan plan, const void *rho, void *
     b.in2 = rho;
     b.grad_e = grad_e;
     b.out = grad_rho;
-    // The chains run side by side when their two spectra fit the last-level
-    // cache together, and neither forks side streams of its own: every pass is
-    // one launch group (single plans; batched plans whose problems all take
-    // multi-plan launches) or the groups run in order (capture).  Otherwise, or without
-    // the plan's streams, in order on the caller's stream: a spectrum that
-    // fits the cache alone stays there from one pass to the next, which two
-    // chains side by side would give up.
-    const bool single_groups =
-        (plan->lr2c.size() == 1 && plan->lb.size() == 1 && plan->la.size() == 1) || under_capture(s);
+    // The chains run side by side when neither forks side streams of its own
+    // and their two spectra fit the last-level cache together: every pass one
+    // launch group (single plans; batched plans whose problems all take
+    // multi-plan launches).  Otherwise, or without the plan's streams, in
+    // order on the caller's stream: a spectrum that fits the cache alone stays
+    // there from one pass to the next, which two chains side by side would
+    // give up.  Under capture several groups run in order and leave gaps that
+    // the other chain fills, also while the spectra take up to twice the cache
+    // (24 untuned problems, replayed: 1,361 us in order, 1,204 side by side).
+    const bool single_groups = plan->lr2c.size() == 1 && plan->lb.size() == 1 && plan->la.size() == 1;
     const size_t spec_bytes = size_t(plan->spec_count) * (plan->fp64 ? 16 : 8);
-    if (!plan->side_ready || !single_groups || 2 * spec_bytes > kOverlapCacheBytes) {
+    const bool beside = single_groups ? 2 * spec_bytes <= kOverlapCacheBytes
+                                      : spec_bytes <= kOverlapCacheBytes && under_capture(s);
+    if (!plan->side_ready || !beside) {
         // in order, on the one spectrum (the cache still holds it)
         if ((st = solve_chain(plan, a, e_h, s)) != HARTREE_OK) return st;
         b.spec = a.spec;

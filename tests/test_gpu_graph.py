@@ -212,6 +212,27 @@ def test_solve_backward_concurrent_chains(H, prec, kind):
         assert_same(step.outputs(), ref, "solve_backward replay %d" % rep)
 
 
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_captured_groups_in_order(H, prec):
+    """A batched plan whose passes have several launch groups: under capture
+    the groups are recorded in order and hartree_solve_backward's chains as two
+    branches; every replay equals the eager solve and backward bit for bit."""
+    probs = [inputs.small_problem(d, n, seed=sd, L=L) for d, n, sd, L in BATCHED]
+    say("case captured groups", prec, [q.dims for q in probs])
+    ref_step, step = Step(H, probs, prec), Step(H, probs, prec, fused=True)
+    ref_step.run()
+    torch.cuda.synchronize()
+    ref = ref_step.outputs()
+    step.plan.capture(lambda: step.run(rebind=True))
+    torch.cuda.synchronize()
+    for rep in range(3):
+        step.scribble()
+        torch.cuda.synchronize()
+        step.plan.replay()
+        torch.cuda.synchronize()
+        assert_same(step.outputs(), ref, "replay %d" % rep)
+
+
 def test_solve_backward_zero_gradient_and_errors(H):
     """No upstream gradient: grad_rho is zero and V, E_H are the solve's;
     v aliasing grad_v or grad_rho is rejected."""
