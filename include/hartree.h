@@ -292,10 +292,12 @@ hartree_status hartree_graph_launch(hartree_plan plan, void *stream);
  *                            threads than a workgroup has, or more LDS than
  *                            the device allows); with a workspace bound it
  *                            re-uploads the problem descriptors (synchronous);
- *   hartree_plan_tune        times every valid choice per (axis, length), the
+ *   hartree_plan_tune        times the valid choices per (axis, length), the
  *                            forward and inverse passes of that axis, `reps`
  *                            times each on `stream`, keeps the fastest and
- *                            applies it.  scratch: a device grid of the plan's
+ *                            applies it; in FP32 only choices that give V and
+ *                            grad_rho alike bit for bit, so that tuning a plan
+ *                            again does not change them.  scratch: a device grid of the plan's
  *                            precision and total grid size, overwritten.
  *                            Synchronous; needs a bound workspace. */
 hartree_status hartree_plan_get_config(hartree_plan plan, int32_t *cfg);

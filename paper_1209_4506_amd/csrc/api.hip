@@ -14,6 +14,7 @@
 #include "fft_core.hpp"
 #include "partition.hpp"
 #include "kernels.hpp"
+#include "tune.hpp"
 
 using namespace hartree;
 
@@ -1458,82 +1459,45 @@ hartree_status hartree_plan_tune(hartree_plan plan, void *grid, int32_t reps, vo
         }
         return true;
     };
-    // one key per (axis, length): every problem with that length takes the choice
+    // the fastest of a set of whole configurations along axis x, into cfg;
+    // false when none applies
+    auto take_fastest = [&](int x, const std::vector<std::vector<int32_t>> &trials) -> bool {
+        float best = 0.0f;
+        const std::vector<int32_t> *at = nullptr;
+        for (const auto &trial : trials) {
+            float ms = 0.0f;
+            if (!time_axis(x, trial, ms)) {
+                if (result != HARTREE_OK) return false;
+                continue;
+            }
+            if (!at || ms < best) {
+                best = ms;
+                at = &trial;
+            }
+        }
+        if (at) cfg = *at;
+        return at != nullptr;
+    };
+    auto set = [&](std::vector<int32_t> &c, int q, int x, int id, int lp, int pad) {
+        c[3 * (3 * q + x)] = id;
+        c[3 * (3 * q + x) + 1] = lp;
+        c[3 * (3 * q + x) + 2] = pad;
+    };
     for (int x = 2; x >= 0 && result == HARTREE_OK; --x) {
         std::vector<int> lengths;
         for (int q = 0; q < plan->nprob; ++q)
             if (std::find(lengths.begin(), lengths.end(), plan->desc[q].dims[x]) == lengths.end())
                 lengths.push_back(plan->desc[q].dims[x]);
-        for (int n : lengths) {
-            struct Cand {
-                int id, lp, pad;
-            };
-            std::vector<Cand> cand;
-            std::vector<int> r;
-            for (int id = -1; id < plan_table_size(); ++id)
-                for (int lp = 0; lp <= 6; ++lp)
-                    for (int pad = 0; pad <= (x == 2 ? 0 : 2); ++pad)
-                        if (choice_radices(plan, x, n, id, lp, pad, r) &&
-                            (id >= 0 || find_plan(r.data(), int(r.size())) < 0))
-                            cand.push_back({id, lp, pad});
-            struct Timed {
-                int id;
-                float ms;
-                std::vector<int32_t> cfg;
-            };
-            std::vector<Timed> fastest;  // of each radix plan, in the order of their ids
-            float best = 0.0f;
-            for (const auto &c : cand) {
-                std::vector<int32_t> trial = cfg;
-                for (int q = 0; q < plan->nprob; ++q)
-                    if (plan->desc[q].dims[x] == n) {
-                        trial[3 * (3 * q + x)] = c.id;
-                        trial[3 * (3 * q + x) + 1] = c.lp;
-                        trial[3 * (3 * q + x) + 2] = c.pad;
-                    }
-                float ms = 0.0f;
-                if (!time_axis(x, trial, ms)) {
-                    if (result != HARTREE_OK) break;
-                    continue;
-                }
-                if (fastest.empty() || fastest.back().id != c.id) fastest.push_back({c.id, ms, trial});
-                else if (ms < fastest.back().ms) fastest.back() = {c.id, ms, trial};
-                if (best == 0.0f || ms < best) best = ms;
-            }
-            // Radix plans of one length round differently in FP32, and two are
-            // often closer than a timing repeats (360 along a: 152.3 and 153.6
-            // us, timings 3 % apart).  So that tuning again gives the same
-            // values, those near the least time are timed four times more, in
-            // turn, and of the ones then within 1 % of it the first is taken.
-            const float near = (plan->fp64 ? 1.0f : 1.03f) * best;
-            fastest.erase(std::remove_if(fastest.begin(), fastest.end(), [&](const Timed &t) { return t.ms > near; }),
-                          fastest.end());
-            for (int round = 0; round < 4 && fastest.size() > 1 && result == HARTREE_OK; ++round)
-                for (auto &t : fastest) {
-                    float ms = 0.0f;
-                    if (!time_axis(x, t.cfg, ms)) break;
-                    t.ms = std::min(t.ms, ms);
-                    best = std::min(best, ms);
-                }
-            std::vector<int32_t> best_cfg = cfg;
-            for (const auto &t : fastest)
-                if (t.ms <= (plan->fp64 ? 1.0f : 1.01f) * best) {
-                    best_cfg = t.cfg;
-                    break;
-                }
-            if (result != HARTREE_OK) break;
-            cfg = best_cfg;
-        }
-        // batched FP32 plans: the axis as one multi-plan launch per pass
-        // (every length on its compiled plan at the multi tile width), kept
-        // when it times faster than the per-length choices
-        if (result == HARTREE_OK && plan->nprob > 1 && !plan->fp64) {
-            float ms_best = 0.0f;
-            if (!time_axis(x, cfg, ms_best)) ms_best = 0.0f;
+        // FP32 batches whose lengths all have a plan of the axis' multi-plan
+        // list: one multi-plan launch per pass (along a and b only when there
+        // are several lengths; problems of one length are one launch anyway)
+        if (plan->nprob > 1 && !plan->fp64 && (x == 2 || lengths.size() > 1)) {
+            bool whole = true, sized = false;
+            std::vector<std::vector<int32_t>> trials;
+            for (int n : lengths) sized = sized || multi_sized_only(x, n);
             for (int lp : {multi_log_p(x, 0), multi_log_p(x, 1), kMultiAutoLog}) {
-                if (result != HARTREE_OK || ms_best == 0.0f) break;
+                if (sized && lp != kMultiAutoLog) continue;
                 std::vector<int32_t> trial = cfg;
-                bool whole = true;
                 for (int q = 0; q < plan->nprob && whole; ++q) {
                     const int n = plan->desc[q].dims[x];
                     int id = -1;
@@ -1549,16 +1513,28 @@ hartree_status hartree_plan_tune(hartree_plan plan, void *grid, int32_t reps, vo
                     if (lp == kMultiAutoLog)
                         for (l2 = 0; (1 << l2) < multi_auto_p(n, x); ++l2) {
                         }
-                    trial[3 * (3 * q + x)] = id;
-                    trial[3 * (3 * q + x) + 1] = l2;
-                    trial[3 * (3 * q + x) + 2] = 0;
+                    set(trial, q, x, id, l2, 0);
                 }
-                float ms = 0.0f;
-                if (whole && time_axis(x, trial, ms) && ms < ms_best) {
-                    ms_best = ms;
-                    cfg = trial;
-                }
+                if (whole) trials.push_back(trial);
             }
+            if (take_fastest(x, trials) || result != HARTREE_OK) continue;
+        }
+        // otherwise per length: every problem with that length takes the choice
+        for (int n : lengths) {
+            std::vector<std::vector<int32_t>> trials;
+            std::vector<int> r;
+            for (int id = -1; id < plan_table_size(); ++id)
+                for (int lp = 0; lp <= 6; ++lp)
+                    for (int pad = 0; pad <= (x == 2 ? 0 : 2); ++pad) {
+                        if (!choice_radices(plan, x, n, id, lp, pad, r) || (id < 0 && find_plan(r.data(), int(r.size())) >= 0) ||
+                            !tune_times(plan->fp64, x, n, id, lp, pad))
+                            continue;
+                        trials.push_back(cfg);
+                        for (int q = 0; q < plan->nprob; ++q)
+                            if (plan->desc[q].dims[x] == n) set(trials.back(), q, x, id, lp, pad);
+                    }
+            take_fastest(x, trials);
+            if (result != HARTREE_OK) break;
         }
     }
     (void)hipEventDestroy(ev[0]);
