@@ -120,8 +120,10 @@ hartree_status hartree_plan_grid_offset(hartree_plan plan, int32_t p, int64_t *o
  * multi-plan launch takes, and the backward chain of
  * hartree_solve_backward) starts
  * after the work already queued on the caller's stream and is joined back
- * before the call returns, so calls stay ordered on the caller's stream
- * (under capture the forked work becomes parallel branches of the graph).
+ * before the call returns, so calls stay ordered on the caller's stream.
+ * Under capture the launch groups run in order on the caller's stream; only
+ * the chains of hartree_solve_backward, where that call runs them side by
+ * side, become two branches of the graph.
  * If the streams cannot be created everything runs on the caller's stream;
  * results are the same either way.  The plan owns the streams until
  * hartree_plan_destroy. */

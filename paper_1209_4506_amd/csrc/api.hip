@@ -688,7 +688,8 @@ bool under_capture(hipStream_t s)
 // captured step of six problems, forked in four and five groups to a pass,
 // ended its process with a segmentation fault in host code, as another had
 // inside the runtime's recording of the graph, and no fault of these calls was
-// found.  (hartree_solve_backward's two chains are two branches either way.)
+// found.  (Plans with one group per pass record hartree_solve_backward's two
+// chains as two branches: one fork and one join, which no capture failed on.)
 hipError_t run_group(hartree_plan p, const std::vector<Launch> &groups, PassKind kind, PassArgs a, hipStream_t s)
 {
     return timed(p, kernel_id(kind), s, [&]() -> hipError_t {
@@ -1031,20 +1032,19 @@ hartree_status hartree_solve_backward(hartree_plan plan, const void *rho, void *
     b.in2 = rho;
     b.grad_e = grad_e;
     b.out = grad_rho;
-    // The chains run side by side when neither forks side streams of its own
-    // and their two spectra fit the last-level cache together: every pass one
-    // launch group (single plans; batched plans whose problems all take
-    // multi-plan launches).  Otherwise, or without the plan's streams, in
-    // order on the caller's stream: a spectrum that fits the cache alone stays
-    // there from one pass to the next, which two chains side by side would
-    // give up.  Under capture several groups run in order and leave gaps that
-    // the other chain fills, also while the spectra take up to twice the cache
-    // (24 untuned problems, replayed: 1,361 us in order, 1,204 side by side).
+    // The chains run side by side when their two spectra fit the last-level
+    // cache together, and every pass is one launch group (single plans; batched
+    // plans whose problems all take multi-plan launches), so that the backward
+    // chain forks no side streams of its own.  Otherwise, or without the plan's
+    // streams, in order on the caller's stream: a spectrum that fits the cache
+    // alone stays there from one pass to the next, which two chains side by
+    // side would give up.  Under capture plans with several groups would gain
+    // (24 untuned problems, replayed: 1,361 us in order, 1,204 with the chains as
+    // two branches), but a capture of such a plan with branches has ended its
+    // process twice, from no known cause (see run_group): they stay in order.
     const bool single_groups = plan->lr2c.size() == 1 && plan->lb.size() == 1 && plan->la.size() == 1;
     const size_t spec_bytes = size_t(plan->spec_count) * (plan->fp64 ? 16 : 8);
-    const bool beside = single_groups ? 2 * spec_bytes <= kOverlapCacheBytes
-                                      : spec_bytes <= kOverlapCacheBytes && under_capture(s);
-    if (!plan->side_ready || !beside) {
+    if (!plan->side_ready || !single_groups || 2 * spec_bytes > kOverlapCacheBytes) {
         // in order, on the one spectrum (the cache still holds it)
         if ((st = solve_chain(plan, a, e_h, s)) != HARTREE_OK) return st;
         b.spec = a.spec;
