@@ -116,26 +116,33 @@ void unit_root(long t, long n, double &c, double &s)
     }
 }
 
-// The triangular frame of a cell (ProbDesc::frame and tri): Gram-Schmidt from
-// the row c up, each residual orthogonalized twice so that the frame stays
-// orthonormal in strongly skewed cells too.
-void set_frame(ProbDesc &d)
+// The grid steps of a cell and its triangular frame: Gram-Schmidt from the row c
+// up, each residual orthogonalized twice so that the frame stays orthonormal
+// in strongly skewed cells too.
+GenDesc gen_desc(const ProbDesc &d)
 {
+    GenDesc g;
+    for (int k = 0; k < 9; ++k) {
+        const double e = d.A[k] / d.dims[k / 3];
+        g.step[k] = float(e);
+        g.stepl[k] = float(e - double(g.step[k]));
+    }
     auto dot = [](const double *x, const double *y) { return x[0] * y[0] + x[1] * y[1] + x[2] * y[2]; };
     for (int k = 2; k >= 0; --k) {
         double v[3] = {d.A[3 * k], d.A[3 * k + 1], d.A[3 * k + 2]};
         for (int pass = 0; pass < 2; ++pass)
             for (int m = 2; m > k; --m) {
-                const double *e = d.frame + 3 * m, p = dot(v, e);
+                const double *e = g.frame + 3 * m, p = dot(v, e);
                 for (int c = 0; c < 3; ++c) v[c] -= p * e[c];
             }
         const double len = std::sqrt(dot(v, v));
-        for (int c = 0; c < 3; ++c) d.frame[3 * k + c] = v[c] / len;
+        for (int c = 0; c < 3; ++c) g.frame[3 * k + c] = v[c] / len;
     }
     const double *a = d.A, *b = d.A + 3, *c = d.A + 6;
-    for (int x = 0; x < 3; ++x) d.tri[x] = dot(a, d.frame + 3 * x) / d.dims[0];
-    for (int x = 1; x < 3; ++x) d.tri[2 + x] = dot(b, d.frame + 3 * x) / d.dims[1];
-    d.tri[5] = dot(c, d.frame + 6) / d.dims[2];
+    for (int x = 0; x < 3; ++x) g.tri[x] = dot(a, g.frame + 3 * x) / d.dims[0];
+    for (int x = 1; x < 3; ++x) g.tri[2 + x] = dot(b, g.frame + 3 * x) / d.dims[1];
+    g.tri[5] = dot(c, g.frame + 6) / d.dims[2];
+    return g;
 }
 
 struct Launch {
@@ -178,7 +185,7 @@ struct hartree_plan_s {
     int64_t max_parts = 0;  // E_H partial slots at one pencil per workgroup
     // workspace layout
     size_t o_status = 0, o_desc = 0, o_tw = 0, o_spec = 0, o_parts = 0, o_qsum = 0, o_info = 0, o_counts = 0,
-           o_offsets = 0, o_ends = 0, o_claims = 0, o_cursor = 0, o_list = 0, o_lists = 0, o_bpart = 0, o_slot = 0, o_rec = 0, o_order = 0, o_zero = 0,
+           o_offsets = 0, o_ends = 0, o_claims = 0, o_cursor = 0, o_list = 0, o_lists = 0, o_bpart = 0, o_slot = 0, o_rec = 0, o_gen = 0, o_order = 0, o_zero = 0,
            o_spec2 = 0, ws_size = 0;
     int32_t cap_pa = 0;
     bool wide = false;  // some truncation window can hold two images of one grid point
@@ -497,12 +504,6 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
             d.hfl[k] = float(d.h[k] - double(d.hf[k]));
         }
         for (int k = 0; k < 9; ++k) d.A[k] = A[k];
-        set_frame(d);
-        for (int k = 0; k < 9; ++k) {
-            const double e = A[k] / N[k / 3];
-            d.step[k] = float(e);
-            d.stepl[k] = float(e - double(d.step[k]));
-        }
         d.separable = (ortho && A[0] > 0.0 && A[4] > 0.0 && A[8] > 0.0) ? 1 : 0;
         if (!d.separable) p->general = true;
         // pass tiles: default radix plan and pencils per workgroup per axis
@@ -595,6 +596,7 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
         p->o_bpart = take(24 * size_t(p->capacity));
         p->o_slot = take(4 * size_t(p->capacity));
         if (!p->general) p->o_rec = take((p->fp64 ? sizeof(SlotAtom64) : sizeof(SlotAtom)) * size_t(p->capacity));
+        if (p->general) p->o_gen = take(sizeof(GenDesc) * size_t(nprob));
         if (nprob > 1) p->o_order = take(4 * size_t(p->nbricks));
     }
     // the second spectrum (hartree_solve_backward's backward chain), last,
@@ -740,6 +742,7 @@ SplatArgs splat_args(hartree_plan p, int32_t natoms, const double *pos, const do
     SplatArgs a;
     std::memset(&a, 0, sizeof(a));
     a.desc = reinterpret_cast<const ProbDesc *>(p->ws + p->o_desc);
+    a.gen = p->general ? reinterpret_cast<const GenDesc *>(p->ws + p->o_gen) : nullptr;
     a.nprob = p->nprob;
     a.natoms = natoms;
     if (p->nprob == 1) {
@@ -869,6 +872,12 @@ hartree_status hartree_bind_workspace(hartree_plan plan, void *workspace, size_t
     hipError_t e = hipMemcpy(ws + plan->o_desc, plan->desc.data(), sizeof(ProbDesc) * plan->nprob,
                              hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "uploading plan descriptors");
+    if (plan->general && plan->splat_ok) {
+        std::vector<GenDesc> gen;
+        for (const ProbDesc &d : plan->desc) gen.push_back(gen_desc(d));
+        e = hipMemcpy(ws + plan->o_gen, gen.data(), sizeof(GenDesc) * gen.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) return hip_fail(e, "uploading the cells' grid steps");
+    }
     const size_t ntw = plan->twiddles.size() / 2;
     if (plan->fp64) {
         e = hipMemcpy(ws + plan->o_tw, plan->twiddles.data(), 16 * ntw, hipMemcpyHostToDevice);

@@ -70,14 +70,6 @@ struct ProbDesc {
     float hf[3];        // h as a float ...
     float hfl[3];       // ... and the float of its remainder h - hf
     double A[9];        // cell rows a, b, c (any cell)
-    // triangular frame (any cell): orthonormal rows e1, e2, e3 with e3 along c
-    // and e2 in the plane of b and c, and the grid steps a / Na = tri[0] e1 +
-    // tri[1] e2 + tri[2] e3, b / Nb = tri[3] e2 + tri[4] e3, c / Nc = tri[5] e3
-    // (tri[0], tri[3], tri[5] > 0)
-    double frame[9];
-    double tri[6];
-    float step[9];      // the grid steps a / Na, b / Nb, c / Nc as floats ...
-    float stepl[9];     // ... and the floats of their remainders
     int32_t separable;  // 1: diagonal cell with positive edges (separable splat)
     int32_t pad4;
     int32_t part_off;   // first E_H partial slot of this problem
@@ -87,6 +79,19 @@ struct ProbDesc {
     int32_t pad2;
     int32_t bsz[3];     // brick edge in grid points per axis
     int32_t col_off;    // first column of bricks along c of this problem
+};
+
+// What only the splat kernels of plans with a cell that is not diagonal read
+// of a problem (apart from ProbDesc, which every solve holds in its scratch).
+struct GenDesc {
+    // triangular frame: orthonormal rows e1, e2, e3 with e3 along c and e2 in
+    // the plane of b and c, and the grid steps a / Na = tri[0] e1 + tri[1] e2 +
+    // tri[2] e3, b / Nb = tri[3] e2 + tri[4] e3, c / Nc = tri[5] e3 (tri[0],
+    // tri[3], tri[5] > 0)
+    double frame[9];
+    double tri[6];
+    float step[9];      // the grid steps a / Na, b / Nb, c / Nc as floats ...
+    float stepl[9];     // ... and the floats of their remainders
 };
 
 // Splat bricks, one workgroup each: MI x MJ x MK grid points for the

@@ -96,6 +96,7 @@ constexpr int kClaimStride = 32;  // one cache line per counter
 
 struct SplatArgs {
     const ProbDesc *desc;
+    const GenDesc *gen;     // per problem (general)
     int32_t nprob;
     int32_t natoms;
     int32_t atom_off[kMaxProb + 1];  // prefix atom counts per problem

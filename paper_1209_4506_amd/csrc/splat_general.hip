@@ -6,7 +6,7 @@
 // sphere |d| <= cutoff sigma (the truncation of the CPU reference as well).
 // Most points of a listed brick lie outside the sphere (at 160^3 in the
 // diamond FCC cell 78%), so both precisions first place each atom image's
-// sphere in the problem's triangular frame (ProbDesc tri: the third axis along
+// sphere in the problem's triangular frame (GenDesc tri: the third axis along
 // the cell row c, the second in the plane of b and c, where the points of a
 // run of grid indices lie in a box) and pass over whole runs of points that
 // the sphere does not reach.  A wavefront takes 64 points at a time, its sums
@@ -70,7 +70,7 @@ struct GenImages {
     int count;
 };
 
-__device__ __forceinline__ GenImages gen_images(const AtomInfo &in, const ProbDesc &d, const int g0[3], double rb[3])
+__device__ __forceinline__ GenImages gen_images(const AtomInfo &in, const ProbDesc &d, const GenDesc &gd, const int g0[3], double rb[3])
 {
     GenImages im;
     im.count = 1;
@@ -84,7 +84,7 @@ __device__ __forceinline__ GenImages gen_images(const AtomInfo &in, const ProbDe
         im.mc[x] = im.u0[x] <= in.hi[x] - in.lo[x] ? (in.hi[x] - in.lo[x] - im.u0[x]) / n + 1 : 0;
         im.count *= im.mc[x];
     }
-    for (int x = 0; x < 3; ++x) im.r[x] = rb[0] * d.frame[3 * x] + rb[1] * d.frame[3 * x + 1] + rb[2] * d.frame[3 * x + 2];
+    for (int x = 0; x < 3; ++x) im.r[x] = rb[0] * gd.frame[3 * x] + rb[1] * gd.frame[3 * x + 1] + rb[2] * gd.frame[3 * x + 2];
     return im;
 }
 
@@ -106,7 +106,7 @@ struct GenShift {
     int u[3];
     double p[3];
 };
-__device__ __forceinline__ GenShift gen_shift(const GenImages &im, const ProbDesc &d, int i)
+__device__ __forceinline__ GenShift gen_shift(const GenImages &im, const ProbDesc &d, const GenDesc &gd, int i)
 {
     GenShift s;
     for (int x = 0; x < 3; ++x) s.u[x] = im.u0[x];
@@ -117,19 +117,19 @@ __device__ __forceinline__ GenShift gen_shift(const GenImages &im, const ProbDes
         s.u[0] += u * d.dims[0];
     }
     const double ga = s.u[0], gb = s.u[1], gc = s.u[2];
-    s.p[0] = ga * d.tri[0] - im.r[0];
-    s.p[1] = ga * d.tri[1] + gb * d.tri[3] - im.r[1];
-    s.p[2] = ga * d.tri[2] + gb * d.tri[4] + gc * d.tri[5] - im.r[2];
+    s.p[0] = ga * gd.tri[0] - im.r[0];
+    s.p[1] = ga * gd.tri[1] + gb * gd.tri[3] - im.r[1];
+    s.p[2] = ga * gd.tri[2] + gb * gd.tri[4] + gc * gd.tri[5] - im.r[2];
     return s;
 }
 
 // squared distance from the atom to the box (in the triangular frame) that
 // holds the points at offsets o .. o + e (inclusive, per axis) from the
 // brick's first point
-__device__ __forceinline__ double box_distance2(const ProbDesc &d, const double p[3], const int o[3], double ea, double eb,
+__device__ __forceinline__ double box_distance2(const GenDesc &gd, const double p[3], const int o[3], double ea, double eb,
                                                 double ec)
 {
-    const double *t = d.tri;
+    const double *t = gd.tri;
     const double oa = o[0], ob = o[1], oc = o[2];
     const double b1 = p[0] + oa * t[0], b2 = p[1] + oa * t[1] + ob * t[3], b3 = p[2] + oa * t[2] + ob * t[4] + oc * t[5];
     const double g1 = gap(b1, b1 + ea * t[0]);
@@ -160,13 +160,13 @@ constexpr double kBoxMargin = 1.0001;
 struct GenSteps {
     float e[9], l[9];
 };
-__device__ __forceinline__ GenSteps gen_steps(const ProbDesc &d)
+__device__ __forceinline__ GenSteps gen_steps(const GenDesc &gd)
 {
     GenSteps g;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        g.e[k] = d.step[k];
-        g.l[k] = d.stepl[k];
+        g.e[k] = gd.step[k];
+        g.l[k] = gd.stepl[k];
         asm volatile("" : "+v"(g.e[k]), "+v"(g.l[k]));
     }
     return g;
@@ -177,7 +177,8 @@ struct GenAtom32 {
     GenImages im;
     float rb[3], rbl[3], inv2s2, w, rc2;
 };
-__device__ __forceinline__ GenAtom32 gen_atom32(const SplatArgs &a, const ProbDesc &d, const int g0[3], int64_t e, bool use)
+__device__ __forceinline__ GenAtom32 gen_atom32(const SplatArgs &a, const ProbDesc &d, const GenDesc &gd, const int g0[3], int64_t e,
+                                                bool use)
 {
     GenAtom32 g;
     g.im = no_images();
@@ -186,7 +187,7 @@ __device__ __forceinline__ GenAtom32 gen_atom32(const SplatArgs &a, const ProbDe
     if (!use) return g;
     const AtomInfo in = a.info[a.list_sorted[e]];
     double rb[3];
-    g.im = gen_images(in, d, g0, rb);
+    g.im = gen_images(in, d, gd, g0, rb);
     for (int c = 0; c < 3; ++c) {
         g.rb[c] = float(rb[c]);
         g.rbl[c] = float(rb[c] - double(g.rb[c]));
@@ -219,14 +220,14 @@ __device__ __forceinline__ GenAtom32 lane_atom(const GenAtom32 &g, int q)
 // The images of the lane's entry that reach the box of points o .. o + e: bit
 // i for image i < 32; with more images all of them (bit 31 stands for the
 // images from 31 on).
-__device__ __forceinline__ uint32_t gen_hits(const GenAtom32 &g, const ProbDesc &d, const int o[3],
+__device__ __forceinline__ uint32_t gen_hits(const GenAtom32 &g, const ProbDesc &d, const GenDesc &gd, const int o[3],
                                              double ea, double eb, double ec)
 {
     uint32_t hits = 0;
     for (int i = 0; __any(i < g.im.count && i < 32); ++i) {
         if (i >= g.im.count) continue;
-        const GenShift s = gen_shift(g.im, d, i);
-        if (box_distance2(d, s.p, o, ea, eb, ec) <= kBoxMargin * double(g.rc2)) hits |= 1u << i;
+        const GenShift s = gen_shift(g.im, d, gd, i);
+        if (box_distance2(gd, s.p, o, ea, eb, ec) <= kBoxMargin * double(g.rc2)) hits |= 1u << i;
     }
     return g.im.count > 32 ? 0xffffffffu : hits;
 }
@@ -267,20 +268,21 @@ __global__ __launch_bounds__(256) void k_splat_general32(SplatArgs a)
     const int unit = item % UNITS;
     const int prob = brick_prob(a, b);
     const ProbDesc &d = a.desc[prob];
+    const GenDesc &gd = a.gen[prob];
     const BrickPos p = brick_pos(d, b);
     const int g0[3] = {p.b0 * kMI, p.b1 * kMJ, p.b2 * kMK};
     const int o[3] = {NS * (unit % UI), 8 * ((unit / UI) % (kMJ / 8)), 8 * (unit / (UI * (kMJ / 8)))};
     if (g0[0] + o[0] >= d.dims[0] || g0[1] + o[1] >= d.dims[1] || g0[2] + o[2] >= d.dims[2]) return;
     const int lj = lane >> 3, lk = lane & 7;
-    const GenSteps st = gen_steps(d);
+    const GenSteps st = gen_steps(gd);
     const int64_t off = a.offsets[b];
     const int cnt = int(a.ends[b] - off);
     float acc[NS];
 #pragma unroll
     for (int i = 0; i < NS; ++i) acc[i] = 0.0f;
     for (int c0 = 0; c0 < cnt; c0 += 64) {
-        const GenAtom32 mine = gen_atom32(a, d, g0, off + c0 + lane, c0 + lane < cnt);
-        const uint32_t hits = gen_hits(mine, d, o, NS - 1, 7.0, 7.0);
+        const GenAtom32 mine = gen_atom32(a, d, gd, g0, off + c0 + lane, c0 + lane < cnt);
+        const uint32_t hits = gen_hits(mine, d, gd, o, NS - 1, 7.0, 7.0);
         uint64_t todo = __ballot(hits != 0u);
         while (todo) {
             const int q = __builtin_ctzll(todo);
@@ -289,11 +291,11 @@ __global__ __launch_bounds__(256) void k_splat_general32(SplatArgs a)
             const GenAtom32 at = lane_atom(mine, q);
             for (int im = 0; im < at.im.count; ++im) {
                 if (!((hq >> (im < 31 ? im : 31)) & 1u)) continue;
-                const GenShift s = gen_shift(at.im, d, im);
+                const GenShift s = gen_shift(at.im, d, gd, im);
                 // planes the sphere reaches: lane l tests plane l
                 const int ol[3] = {o[0] + (lane & (NS - 1)), o[1], o[2]};
                 const uint32_t mask =
-                    uint32_t(__ballot(box_distance2(d, s.p, ol, 0.0, 7.0, 7.0) <= kBoxMargin * double(at.rc2)));
+                    uint32_t(__ballot(box_distance2(gd, s.p, ol, 0.0, 7.0, 7.0) <= kBoxMargin * double(at.rc2)));
                 const int u0 = s.u[0] + o[0];
                 const GenColumn col = gen_column(st, at, s.u[1] + o[1] + lj, s.u[2] + o[2] + lk);
 #pragma unroll
@@ -345,6 +347,7 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
     const int share = blockIdx.x - int(b) * split;
     const int prob = brick_prob(a, b);
     const ProbDesc &d = a.desc[prob];
+    const GenDesc &gd = a.gen[prob];
     const int64_t off = a.offsets[b];
     const int cnt = int(a.ends[b] - off);
     const int ways = 4 * split, way = 4 * share + wave;  // entries way, way + ways, ... are this wavefront's
@@ -366,12 +369,12 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
             }
     }
     __syncthreads();
-    const GenSteps st = gen_steps(d);
+    const GenSteps st = gen_steps(gd);
     const int whole[3] = {0, 0, 0};
     for (int c0 = 0; c0 < cnt; c0 += 64 * ways) {
         const int mye = c0 + lane * ways + way;
-        const GenAtom32 mine = gen_atom32(a, d, g0, off + mye, mye < cnt);
-        const uint32_t hits = gen_hits(mine, d, whole, kMI - 1, kMJ - 1, kMK - 1);
+        const GenAtom32 mine = gen_atom32(a, d, gd, g0, off + mye, mye < cnt);
+        const uint32_t hits = gen_hits(mine, d, gd, whole, kMI - 1, kMJ - 1, kMK - 1);
         for (int q = 0; q < 64 && c0 + q * ways + way < cnt; ++q) {
             const uint32_t hq = lane_value(int(hits), q);
             double v[3] = {0.0, 0.0, 0.0};
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
                 // (bit 2 i + j / 8), two kb at a time: lane l tests run l
                 auto runs = [&](const GenShift &s, int kb) {
                     const int ol[3] = {(lane & 31) >> 1, 8 * (lane & 1), 8 * (kb + (lane >> 5))};
-                    return uint64_t(__ballot(box_distance2(d, s.p, ol, 0.0, 7.0, 7.0) <= reach));
+                    return uint64_t(__ballot(box_distance2(gd, s.p, ol, 0.0, 7.0, 7.0) <= reach));
                 };
                 auto column = [&](const GenShift &s, int kb, int jb) {
                     return gen_column(st, at, s.u[1] + 8 * jb + lj, s.u[2] + 8 * kb + lk);
@@ -399,7 +402,7 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
                 };
                 float z[3] = {0.0f, 0.0f, 0.0f}, y[3];
                 const bool one = !MANY || ((hq & (hq - 1)) == 0u && at.im.count <= 32);
-                const GenShift s1 = gen_shift(at.im, d, one ? __builtin_ctz(hq) : 0);
+                const GenShift s1 = gen_shift(at.im, d, gd, one ? __builtin_ctz(hq) : 0);
                 const uint64_t m01 = one ? runs(s1, 0) : 0, m23 = one ? runs(s1, 2) : 0;
 #pragma unroll 1
                 for (int turn = 0; turn < 4; ++turn) {
@@ -427,9 +430,9 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
 #pragma unroll 1
                             for (int im = 0; im < at.im.count; ++im) {
                                 if (!((hq >> (im < 31 ? im : 31)) & 1u)) continue;
-                                const GenShift s = gen_shift(at.im, d, im);
+                                const GenShift s = gen_shift(at.im, d, gd, im);
                                 const int oi[3] = {i >> 1, 8 * (i & 1), 8 * kb};
-                                if (!(box_distance2(d, s.p, oi, 0.0, 7.0, 7.0) <= reach)) continue;
+                                if (!(box_distance2(gd, s.p, oi, 0.0, 7.0, 7.0) <= reach)) continue;
                                 point(column(s, kb, i & 1), float(s.u[0] + (i >> 1)), g, f);
                             }
                         }
@@ -481,16 +484,16 @@ struct GenRows {
     int64_t row;      // its first point in the grid
 };
 
-__device__ __forceinline__ GenRows gen_rows(const ProbDesc &d, const BrickPos &p, int lane)
+__device__ __forceinline__ GenRows gen_rows(const ProbDesc &d, const GenDesc &gd, const BrickPos &p, int lane)
 {
     GenRows r;
     r.g0[0] = p.b0 * kBI;
     r.g0[1] = p.b1 * kBJ;
     r.g0[2] = p.b2 * kBK;
     const int li = lane >> 3, lj = lane & 7;
-    r.r[0] = li * d.tri[0];
-    r.r[1] = li * d.tri[1] + lj * d.tri[3];
-    r.r[2] = li * d.tri[2] + lj * d.tri[4];
+    r.r[0] = li * gd.tri[0];
+    r.r[1] = li * gd.tri[1] + lj * gd.tri[3];
+    r.r[2] = li * gd.tri[2] + lj * gd.tri[4];
     r.inside = r.g0[0] + li < d.dims[0] && r.g0[1] + lj < d.dims[1];
     r.row = (int64_t(r.g0[0] + li) * d.dims[1] + r.g0[1] + lj) * d.dims[2] + r.g0[2];
     return r;
@@ -567,8 +570,8 @@ struct GenAtom64 {
     double sc, w;
     GenRun run;
 };
-__device__ __forceinline__ GenAtom64 gen_atom64(const SplatArgs &a, const ProbDesc &d, const int g0[3], int64_t e, bool use,
-                                                double qc)
+__device__ __forceinline__ GenAtom64 gen_atom64(const SplatArgs &a, const ProbDesc &d, const GenDesc &gd, const int g0[3], int64_t e,
+                                                bool use, double qc)
 {
     GenAtom64 g;
     g.im = no_images();
@@ -577,25 +580,25 @@ __device__ __forceinline__ GenAtom64 gen_atom64(const SplatArgs &a, const ProbDe
     if (use) {
         const AtomInfo &in = a.info[a.list_sorted[e]];
         double rb[3];
-        g.im = gen_images(in, d, g0, rb);
+        g.im = gen_images(in, d, gd, g0, rb);
         g.sc = sqrt(in.inv2s2);
         // finite, so that the points outside the sphere add zero
         g.w = fmin(fmax(in.w, -1.7976931348623157e308), 1.7976931348623157e308);
     }
-    g.run = gen_run(d.tri[5] * g.sc, qc);
+    g.run = gen_run(gd.tri[5] * g.sc, qc);
     return g;
 }
 
 // s of the lane's row and tm of its run at offset ok, for an image of a
 // displacement p; false when the image reaches none of the wavefront's points
-__device__ __forceinline__ bool gen_row(const ProbDesc &d, const GenRows &rows, const double p[3], double sc, double c, int ok,
+__device__ __forceinline__ bool gen_row(const GenDesc &gd, const GenRows &rows, const double p[3], double sc, double c, int ok,
                                         double qc, double &d1, double &d2, double &s, double &tm)
 {
     d1 = p[0] + rows.r[0];
     d2 = p[1] + rows.r[1];
     const double u1 = d1 * sc, u2 = d2 * sc;
     s = rows.inside ? u1 * u1 + u2 * u2 : HUGE_VAL;
-    tm = (p[2] + rows.r[2] + (ok + 4) * d.tri[5]) * sc;
+    tm = (p[2] + rows.r[2] + (ok + 4) * gd.tri[5]) * sc;
     const double far = fmax(fabs(tm) - 4.0 * c, 0.0);
     return __any(fma(far, far, s) <= qc);
 }
@@ -610,7 +613,8 @@ __global__ __launch_bounds__(64 * kWays) void k_splat_general64(SplatArgs a)
     const int64_t b = item / kSeg;
     const int prob = brick_prob(a, b);
     const ProbDesc &d = a.desc[prob];
-    const GenRows rows = gen_rows(d, brick_pos(d, b), lane);
+    const GenDesc &gd = a.gen[prob];
+    const GenRows rows = gen_rows(d, gd, brick_pos(d, b), lane);
     const int o[3] = {0, 0, kRun * (item % kSeg)};
     if (rows.g0[2] + o[2] >= d.dims[2]) return;
     const int64_t off = a.offsets[b];
@@ -621,13 +625,13 @@ __global__ __launch_bounds__(64 * kWays) void k_splat_general64(SplatArgs a)
     for (int k = 0; k < kRun; ++k) acc[k] = 0.0;
     for (int c0 = 0; c0 < cnt; c0 += 64 * kWays) {
         const int mye = c0 + lane * kWays + wave;
-        const GenAtom64 mine = gen_atom64(a, d, rows.g0, off + mye, mye < cnt, qc);
+        const GenAtom64 mine = gen_atom64(a, d, gd, rows.g0, off + mye, mye < cnt, qc);
         for (int i = 0; __any(i < mine.im.count); ++i) {
             GenShift sh;
             bool hit = false;
             if (i < mine.im.count) {
-                sh = gen_shift(mine.im, d, i);
-                hit = box_distance2(d, sh.p, o, 7.0, 7.0, kRun - 1) * mine.sc * mine.sc <= kBoxMargin * qc;
+                sh = gen_shift(mine.im, d, gd, i);
+                hit = box_distance2(gd, sh.p, o, 7.0, 7.0, kRun - 1) * mine.sc * mine.sc <= kBoxMargin * qc;
             }
             uint64_t todo = __ballot(hit);
             while (todo) {
@@ -636,7 +640,7 @@ __global__ __launch_bounds__(64 * kWays) void k_splat_general64(SplatArgs a)
                 const double p[3] = {lane_value(sh.p[0], q), lane_value(sh.p[1], q), lane_value(sh.p[2], q)};
                 const GenRun rn = lane_run(mine.run, q);
                 double d1, d2, s, tm;
-                if (!gen_row(d, rows, p, lane_value(mine.sc, q), rn.c, o[2], qc, d1, d2, s, tm)) continue;
+                if (!gen_row(gd, rows, p, lane_value(mine.sc, q), rn.c, o[2], qc, d1, d2, s, tm)) continue;
                 double t[kRun], e[kRun];
                 bool in[kRun];
                 gen_exps(rn, s, tm, qc, t, in, e);
@@ -688,7 +692,8 @@ __global__ __launch_bounds__(64 * kWays) void k_adjoint_general64(SplatArgs a, i
     const int share = blockIdx.x - int(b) * split;
     const int prob = brick_prob(a, b);
     const ProbDesc &d = a.desc[prob];
-    const GenRows rows = gen_rows(d, brick_pos(d, b), lane);
+    const GenDesc &gd = a.gen[prob];
+    const GenRows rows = gen_rows(d, gd, brick_pos(d, b), lane);
     const int64_t off = a.offsets[b];
     const int cnt = int(a.ends[b] - off);
     const int ways = kWays * split, way = kWays * share + wave;
@@ -705,7 +710,7 @@ __global__ __launch_bounds__(64 * kWays) void k_adjoint_general64(SplatArgs a, i
     const double qc = 0.5 * a.cutoff * a.cutoff;
     for (int c0 = 0; c0 < cnt; c0 += 64 * ways) {
         const int mye = c0 + lane * ways + way;
-        const GenAtom64 mine = gen_atom64(a, d, rows.g0, off + mye, mye < cnt, qc);
+        const GenAtom64 mine = gen_atom64(a, d, gd, rows.g0, off + mye, mye < cnt, qc);
         for (int q = 0; q < 64 && c0 + q * ways + way < cnt; ++q) {
             const GenRun rn = lane_run(mine.run, q);
             const double sc = lane_value(mine.sc, q);
@@ -718,16 +723,16 @@ __global__ __launch_bounds__(64 * kWays) void k_adjoint_general64(SplatArgs a, i
             }
             double f1 = 0.0, f2 = 0.0, f3 = 0.0;
             for (int i = 0; i < im.count; ++i) {
-                const GenShift sh = gen_shift(im, d, i);
+                const GenShift sh = gen_shift(im, d, gd, i);
                 // runs the sphere reaches: lane l < kSeg tests run l
                 const int ol[3] = {0, 0, kRun * (lane & (kSeg - 1))};
                 const uint32_t reach =
-                    uint32_t(__ballot(box_distance2(d, sh.p, ol, 7.0, 7.0, kRun - 1) * sc * sc <= kBoxMargin * qc));
+                    uint32_t(__ballot(box_distance2(gd, sh.p, ol, 7.0, 7.0, kRun - 1) * sc * sc <= kBoxMargin * qc));
 #pragma unroll 1
                 for (int seg = 0; seg < kSeg; ++seg) {
                     if (!((reach >> seg) & 1u) || rows.g0[2] + kRun * seg >= d.dims[2]) continue;
                     double d1, d2, s, tm;
-                    if (!gen_row(d, rows, sh.p, sc, rn.c, kRun * seg, qc, d1, d2, s, tm)) continue;
+                    if (!gen_row(gd, rows, sh.p, sc, rn.c, kRun * seg, qc, d1, d2, s, tm)) continue;
                     double t[kRun], e[kRun];
                     bool in[kRun];
                     gen_exps(rn, s, tm, qc, t, in, e);
@@ -750,7 +755,7 @@ __global__ __launch_bounds__(64 * kWays) void k_adjoint_general64(SplatArgs a, i
             const int64_t slot = off + c0 + q * ways + way;
             if (lane == 63 && slot < a.capacity)
                 for (int x = 0; x < 3; ++x)
-                    a.bpart[slot * 3 + x] = f1 * d.frame[x] + f2 * d.frame[3 + x] + f3 * d.frame[6 + x];
+                    a.bpart[slot * 3 + x] = f1 * gd.frame[x] + f2 * gd.frame[3 + x] + f3 * gd.frame[6 + x];
         }
     }
 }

@@ -71,3 +71,24 @@ def test_solve_noalloc_rejects_large_plans():
     code = H.LIB.hartree_solve_noalloc(plan._h, vp(rho), vp(V), None, None)
     assert code == 5  # HARTREE_ERR_WORKSPACE, before anything is enqueued
     assert "HARTREE_NOALLOC_BYTES" in H.LIB.hartree_last_error().decode()
+
+
+def test_solve_noalloc_up_to_its_size():
+    """A batch that leaves 3,584 bytes of the scratch: 32 half spectra of 80 x 98
+    x 33, the tables and descriptors."""
+    import paper_1209_4506_amd.hartree as H
+
+    say("case no-alloc solve, a batch that fills the scratch")
+    dims = np.array([(80, 98, 64)] * 32)
+    cells = np.stack([np.diag([8.0 + 0.1 * q, 9.0, 7.0]) for q in range(32)])
+    ref_plan = H.Plan(cells, dims, precision="fp32", max_atoms=1)
+    plan = H.Plan(cells, dims, precision="fp32", max_atoms=1, bind=False)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    rho = ref_plan.empty_grid().normal_(generator=g)
+    V_ref, E_ref = ref_plan.solve(rho)
+    V, E = torch.empty_like(rho), torch.empty(32, device="cuda", dtype=torch.float64)
+    code = H.LIB.hartree_solve_noalloc(plan._h, vp(rho), vp(V), vp(E), None)
+    assert code == 0, H.LIB.hartree_last_error().decode()
+    torch.cuda.synchronize()
+    assert torch.equal(V, V_ref) and torch.equal(E, E_ref)
