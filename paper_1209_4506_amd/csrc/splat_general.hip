@@ -325,6 +325,77 @@ __global__ __launch_bounds__(256) void k_splat_general32(SplatArgs a)
 // two per SIMD) each brick's work is cut into more, smaller pieces
 constexpr int kFewBricks = 256;
 
+// grad_rho of the brick's points of one kb (zero outside the grid) to LDS
+__device__ __forceinline__ void load_grad32(const SplatArgs &a, const ProbDesc &d, const int g0[3], int kb, int lane,
+                                            float (*gr)[64])
+{
+    const float *src = reinterpret_cast<const float *>(a.grad_rho) + d.grid_off;
+    const int k = g0[2] + 8 * kb + (lane & 7);
+#pragma unroll
+    for (int i = 0; i < kMI; ++i)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb) {
+            const int ia = g0[0] + i, j = g0[1] + 8 * jb + (lane >> 3);
+            const bool in = ia < d.dims[0] && j < d.dims[1] && k < d.dims[2];
+            gr[2 * i + jb][lane] = *(in ? src + (int64_t(ia) * d.dims[1] + j) * d.dims[2] + k : a.zeros);
+        }
+}
+
+// the end of a sum over 8 x 8 lanes (j0, k mod 8) whose rows j0 and j0 ^ 1 are
+// added: over k ^ 4, 2, 1 (shifts within rows of 16 lanes), then over the four
+// pairs of j0 in double
+__device__ __forceinline__ double sum_pairs32(float z)
+{
+    float w = dpp_plus<0x104, 0xf>(z);
+    w = dpp_plus<0x102, 0xf>(w);
+    w = dpp_plus<0x101, 0xf>(w);
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v += double(lane_value(w, 16 * r));
+    return v;
+}
+
+// one point of the adjoint: d and grad_rho exp(-|d|^2 / (2 sigma^2)) into the sums
+__device__ __forceinline__ void adjoint_point(const GenSteps &st, const GenAtom32 &at, const GenColumn &col, float ua, float g,
+                                              float (&f)[3])
+{
+    float dv[3];
+    const float d2 = gen_point(st, at, col, ua, dv);
+    const float e = expf(-d2 * at.inv2s2);
+    // (selected after the product: a non-finite grad_rho beyond the sphere
+    // does not reach the atom)
+    const float t = d2 <= at.rc2 ? g * e : 0.0f;
+#pragma unroll
+    for (int x = 0; x < 3; ++x) f[x] = __builtin_fmaf(dv[x], t, f[x]);
+}
+
+// An entry of which several images reach the brick, over the points of one kb
+// (gr: their grad_rho, k0 = 8 kb): run by run, the images in order, 64 of them
+// tested against a run at once, one per lane.
+__device__ __forceinline__ void adjoint_images(const GenSteps &st, const ProbDesc &d, const GenDesc &gd, const GenAtom32 &at,
+                                               double reach, const float (*gr)[64], int k0, int lane, float (&f)[3])
+{
+    const int lj = lane >> 3, lk = lane & 7, count = at.im.count;
+    GenShift s = gen_shift(at.im, d, gd, lane < count ? lane : 0);
+#pragma unroll 1
+    for (int i = 0; i < 2 * kMI; ++i) {
+        const float g = gr[i][lane];
+        const int o[3] = {i >> 1, 8 * (i & 1), k0};
+#pragma unroll 1
+        for (int im = 0; im < count; im += 64) {
+            if (count > 64) s = gen_shift(at.im, d, gd, im + lane < count ? im + lane : 0);
+            uint64_t m = __ballot(im + lane < count && box_distance2(gd, s.p, o, 0.0, 7.0, 7.0) <= reach);
+            while (m) {
+                const int l = __builtin_ctzll(m);
+                m &= m - 1;
+                const int ua = lane_value(s.u[0], l) + o[0], ub = lane_value(s.u[1], l) + o[1] + lj,
+                          uc = lane_value(s.u[2], l) + o[2] + lk;
+                adjoint_point(st, at, gen_column(st, at, ub, uc), float(ua), g, f);
+            }
+        }
+    }
+}
+
 // Adjoint: per list slot the partial sum over the brick's points of grad_rho
 // exp(-|d|^2 / (2 sigma^2)) d (the caller scales by w / sigma^2).  grad_rho of
 // the brick lies in LDS; each wavefront takes list entries of its own (the
@@ -355,19 +426,7 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
     const BrickPos p = brick_pos(d, b);
     const int g0[3] = {p.b0 * kMI, p.b1 * kMJ, p.b2 * kMK};
     const int lj = lane >> 3, lk = lane & 7;
-    {
-        // zero outside the grid
-        const float *src = reinterpret_cast<const float *>(a.grad_rho) + d.grid_off;
-        const int k = g0[2] + 8 * wave + lk;
-#pragma unroll
-        for (int i = 0; i < kMI; ++i)
-#pragma unroll
-            for (int jb = 0; jb < 2; ++jb) {
-                const int ia = g0[0] + i, j = g0[1] + 8 * jb + lj;
-                const bool in = ia < d.dims[0] && j < d.dims[1] && k < d.dims[2];
-                gr[wave][2 * i + jb][lane] = *(in ? src + (int64_t(ia) * d.dims[1] + j) * d.dims[2] + k : a.zeros);
-            }
-    }
+    load_grad32(a, d, g0, wave, lane, gr[wave]);
     __syncthreads();
     const GenSteps st = gen_steps(gd);
     const int whole[3] = {0, 0, 0};
@@ -390,16 +449,6 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
                 auto column = [&](const GenShift &s, int kb, int jb) {
                     return gen_column(st, at, s.u[1] + 8 * jb + lj, s.u[2] + 8 * kb + lk);
                 };
-                auto point = [&](const GenColumn &col, float ua, float g, float (&f)[3]) {
-                    float dv[3];
-                    const float d2 = gen_point(st, at, col, ua, dv);
-                    const float e = expf(-d2 * at.inv2s2);
-                    // (selected after the product: a non-finite grad_rho
-                    // beyond the sphere does not reach the atom)
-                    const float t = d2 <= at.rc2 ? g * e : 0.0f;
-#pragma unroll
-                    for (int x = 0; x < 3; ++x) f[x] = __builtin_fmaf(dv[x], t, f[x]);
-                };
                 float z[3] = {0.0f, 0.0f, 0.0f}, y[3];
                 const bool one = !MANY || ((hq & (hq - 1)) == 0u && at.im.count <= 32);
                 const GenShift s1 = gen_shift(at.im, d, gd, one ? __builtin_ctz(hq) : 0);
@@ -418,24 +467,11 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
                             m &= ~(3u << (2 * i));
                             const float ua = float(u0 + i);
                             const float ga = gr[kb][2 * i][lane], gb = gr[kb][2 * i + 1][lane];
-                            if (two & 1u) point(col0, ua, ga, f);
-                            if (two & 2u) point(col1, ua, gb, f);
+                            if (two & 1u) adjoint_point(st, at, col0, ua, ga, f);
+                            if (two & 2u) adjoint_point(st, at, col1, ua, gb, f);
                         }
                     } else {
-                        // several images reach the brick: point by point, the
-                        // images in order
-#pragma unroll 1
-                        for (int i = 0; i < 2 * kMI; ++i) {
-                            const float g = gr[kb][i][lane];
-#pragma unroll 1
-                            for (int im = 0; im < at.im.count; ++im) {
-                                if (!((hq >> (im < 31 ? im : 31)) & 1u)) continue;
-                                const GenShift s = gen_shift(at.im, d, gd, im);
-                                const int oi[3] = {i >> 1, 8 * (i & 1), 8 * kb};
-                                if (!(box_distance2(gd, s.p, oi, 0.0, 7.0, 7.0) <= reach)) continue;
-                                point(column(s, kb, i & 1), float(s.u[0] + (i >> 1)), g, f);
-                            }
-                        }
+                        adjoint_images(st, d, gd, at, reach, gr[kb], 8 * kb, lane, f);
                     }
 #pragma unroll
                     for (int x = 0; x < 3; ++x) {
@@ -448,16 +484,86 @@ __global__ __launch_bounds__(256) void k_adjoint_general32(SplatArgs a, int spli
                     }
                 }
 #pragma unroll
-                for (int x = 0; x < 3; ++x) {
-                    // k ^ 4, 2, 1 into k = 0 (shifts within rows of 16 lanes)
-                    float w = dpp_plus<0x104, 0xf>(z[x]);
-                    w = dpp_plus<0x102, 0xf>(w);
-                    w = dpp_plus<0x101, 0xf>(w);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) v[x] += double(lane_value(w, 16 * r));
-                }
+                for (int x = 0; x < 3; ++x) v[x] = sum_pairs32(z[x]);
             }
             const int64_t slot = off + c0 + q * ways + way;
+            if (lane < 3 && slot < a.capacity) a.bpart[slot * 3 + lane] = lane == 0 ? v[0] : (lane == 1 ? v[1] : v[2]);
+        }
+    }
+}
+
+// The same for plans of few bricks whose atoms may have several images over one:
+// few entries to go round, and up to hundreds of images each.  The workgroup
+// takes an entry together, a wavefront per kb, and the wavefronts in turn
+// combine an entry's four sums, in the order above.
+// (us; one wavefront per entry, before 64 images were tested at once / this: 2
+// atoms, 343 and more images each, on 16^3 3,684 / 177; 6 on 20^3 1,928 / 115; 60 on
+// 80^3 121 / 59; 200 on 108^3, 196 bricks, 110 / 106; 400 on 128^3, 256 bricks, 157 / 165)
+__global__ __launch_bounds__(256) void k_adjoint_images32(SplatArgs a, int split)
+{
+    __shared__ float gr[4][2 * kMI][64];  // [kb][2 i + j / 8][lane (j0, k mod 8)]
+    __shared__ float part[2][4][3][64];   // [entry parity][kb][x][lane]
+    const int kb = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int64_t b = blockIdx.x / split;
+    const int share = blockIdx.x - int(b) * split;
+    const int prob = brick_prob(a, b);
+    const ProbDesc &d = a.desc[prob];
+    const GenDesc &gd = a.gen[prob];
+    const int64_t off = a.offsets[b];
+    const int cnt = int(a.ends[b] - off);
+    if (share >= cnt) return;  // entries share, share + split, ... are this workgroup's
+    const BrickPos p = brick_pos(d, b);
+    const int g0[3] = {p.b0 * kMI, p.b1 * kMJ, p.b2 * kMK};
+    const int lj = lane >> 3, lk = lane & 7;
+    load_grad32(a, d, g0, kb, lane, gr[kb]);
+    __syncthreads();
+    const GenSteps st = gen_steps(gd);
+    const int whole[3] = {0, 0, 0};
+    int turn = 0;  // entries with an image in reach so far
+    for (int c0 = 0; c0 < cnt; c0 += 64 * split) {
+        const int mye = c0 + lane * split + share;
+        const GenAtom32 mine = gen_atom32(a, d, gd, g0, off + mye, mye < cnt);
+        const uint32_t hits = gen_hits(mine, d, gd, whole, kMI - 1, kMJ - 1, kMK - 1);
+        for (int q = 0; q < 64 && c0 + q * split + share < cnt; ++q) {
+            const uint32_t hq = lane_value(int(hits), q);
+            const int64_t slot = off + c0 + q * split + share;
+            double v[3] = {0.0, 0.0, 0.0};
+            if (hq) {
+                const GenAtom32 at = lane_atom(mine, q);
+                const double reach = kBoxMargin * double(at.rc2);
+                float f[3] = {0.0f, 0.0f, 0.0f};
+                if ((hq & (hq - 1)) == 0u && at.im.count <= 32) {
+                    // one image: lane l < 32 tests run l of this kb
+                    const GenShift s = gen_shift(at.im, d, gd, __builtin_ctz(hq));
+                    const int ol[3] = {(lane & 31) >> 1, 8 * (lane & 1), 8 * kb};
+                    uint32_t m = uint32_t(__ballot(box_distance2(gd, s.p, ol, 0.0, 7.0, 7.0) <= reach));
+                    const GenColumn col0 = gen_column(st, at, s.u[1] + lj, s.u[2] + 8 * kb + lk),
+                                    col1 = gen_column(st, at, s.u[1] + 8 + lj, s.u[2] + 8 * kb + lk);
+                    while (m) {
+                        const int i = __builtin_ctz(m);
+                        m &= m - 1;
+                        adjoint_point(st, at, i & 1 ? col1 : col0, float(s.u[0] + (i >> 1)), gr[kb][i][lane], f);
+                    }
+                } else {
+                    adjoint_images(st, d, gd, at, reach, gr[kb], 8 * kb, lane, f);
+                }
+                // (the wavefront that combines entry n has read part[n & 1]
+                // when it comes to the barrier of entry n + 1, and entry n + 2
+                // is written there after that)
+                float (&pt)[4][3][64] = part[turn & 1];
+#pragma unroll
+                for (int x = 0; x < 3; ++x) pt[kb][x][lane] = dpp_plus<0x128, 0xf>(f[x]);
+                __syncthreads();
+                if ((turn++ & 3) != kb) continue;
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    float z = pt[0][x][lane] + pt[2][x][lane];
+                    z += pt[1][x][lane] + pt[3][x][lane];
+                    v[x] = sum_pairs32(z);
+                }
+            } else if (kb != 0) {
+                continue;
+            }
             if (lane < 3 && slot < a.capacity) a.bpart[slot * 3 + lane] = lane == 0 ? v[0] : (lane == 1 ? v[1] : v[2]);
         }
     }
@@ -781,7 +887,9 @@ hipError_t run_adjoint_general(const SplatArgs &a, hipStream_t s)
         if (nb >= kFewBricks && nb < 4 * kFewBricks) split = 4;
         hipLaunchKernelGGL(k_adjoint_general64, dim3(nb * split), dim3(64 * kWays), 0, s, a, split);
     } else {
-        if (a.many)
+        if (a.many && nb < kFewBricks)
+            hipLaunchKernelGGL(k_adjoint_images32, dim3(nb * split), dim3(256), 0, s, a, split);
+        else if (a.many)
             hipLaunchKernelGGL(k_adjoint_general32<true>, dim3(nb * split), dim3(256), 0, s, a, split);
         else
             hipLaunchKernelGGL(k_adjoint_general32<false>, dim3(nb * split), dim3(256), 0, s, a, split);

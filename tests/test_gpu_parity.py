@@ -207,6 +207,43 @@ def test_general_cell_edges(H, oracle_mod, prec, case):
     assert torch.equal(one.splat_adjoint(pos, Z, sig, to_dev(g, plan.dtype)), clean)
 
 
+# (cell, grid, atoms, widths): hundreds of images of an atom over the bricks of a
+# small cell; several images and more than 256 bricks; one image at most, more
+# than 256 FP32 and 1,024 FP64 bricks, none of the lengths a multiple of the
+# brick; 270 FP64 bricks
+GENERAL_IMAGES = {
+    "hundreds": ([[3.0, 0.0, 0.0], [0.75, 3.3, 0.0], [-0.4, 0.5, 2.7]], (16, 15, 18), 3, (0.8, 1.0)),
+    "long": ([[3.0, 0.0, 0.0], [0.5, 36.0, 0.0], [-0.3, 2.0, 140.0]], (15, 180, 700), 40, (0.5, 0.8)),
+    "single": ([[19.6, 0.0, 0.0], [4.0, 20.0, 0.0], [-3.0, 4.0, 50.0]], (98, 100, 252), 150, (0.3, 0.5)),
+    "split": ([[14.4, 0.0, 0.0], [4.0, 16.0, 0.0], [-2.7, 3.6, 18.0]], (72, 80, 90), 60, (0.6, 1.0)),
+}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("case", list(GENERAL_IMAGES))
+def test_general_cell_images(H, oracle_mod, prec, case):
+    """The kernels of cells that are not diagonal by the number of bricks and of
+    images: density and forces against the oracle (tolerances of the other
+    parity tests)."""
+    say("case general cell images", prec, case)
+    cell, dims, natoms, sig_range = GENERAL_IMAGES[case]
+    p = inputs.small_cell_problem(cell, dims, natoms, seed=45, sig=sig_range)
+    plan = H.Plan(p.cell, p.dims, precision=prec, max_atoms=p.natoms, max_sigma=sig_range[1])
+    pos, Z, sig = _atoms(p)
+    rho = plan.splat(pos, Z, sig).double().cpu().numpy()
+    ref = oracle_mod.splat(p.cell.reshape(9), p.dims, p.pos, p.Z, p.sigma)
+    nb = oracle_mod.splat(p.cell.reshape(9), p.dims, p.pos, p.Z, p.sigma, subtract_background=False)
+    e = np.abs(rho - ref).max() / np.abs(nb).max()
+    g = oracle_mod.poisson(p.cell.reshape(9), ref)[0].astype(np.float32 if prec == "fp32" else np.float64)
+    got = plan.splat_adjoint(pos, Z, sig, to_dev(g, plan.dtype)).cpu().numpy()
+    want = oracle_mod.splat_adjoint(p.cell.reshape(9), p.pos, p.Z, p.sigma, g.astype(np.float64))
+    ef = np.abs(got - want).max() / np.abs(want).max()
+    say("  rho max-rel %.3e  grad max-rel %.3e" % (e, ef))
+    assert plan.device_status() == 0
+    assert e <= (1e-13 if prec == "fp64" else 1e-6)
+    assert ef <= (1e-10 if prec == "fp64" else 1e-5)
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_many_atoms_one_problem(H, oracle_mod, prec):
     """33,000 atoms in one problem, more than the binning's bitmap ranks cover
