@@ -14,6 +14,7 @@
 #include "fft_core.hpp"
 #include "partition.hpp"
 #include "kernels.hpp"
+#include "bin_rule.hpp"
 #include "tune.hpp"
 
 using namespace hartree;
@@ -172,6 +173,7 @@ struct hartree_plan_s {
     int nparts = 0;
     int64_t nbricks = 0;
     int32_t ncols = 0;
+    std::vector<BinShape> bins;  // per problem (atoms: of the call)
     int64_t capacity = 0;
     std::vector<Launch> lr2c, lb, la;  // P1/P5 (axis c), P2/P4 (axis b), P3 (axis a)
     // per problem and axis (a, b, c): compiled radix plan (-1: run-time
@@ -531,6 +533,7 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
         // point-by-point kernels)
         const bool small = p->fp64 && any_general;
         const int bsz[3] = {small ? kBI : kMI, small ? kBJ : kMJ, small ? kBK : kMK};
+        BinShape bin;
         int64_t per_atom = 1;
         for (int x = 0; x < 3; ++x) {
             d.bsz[x] = bsz[x];
@@ -543,6 +546,8 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
             const double w = std::floor(2.0 * p->cutoff * p->max_sigma / h) + 1.0;
             if (w + 1.0 > N[x]) p->wide = true;  // window points (+1 for rounding) exceed the axis
             if (w + 1.0 + bsz[x] > N[x]) p->many = true;
+            bin.nb[x] = d.nbricks[x];
+            bin.touch[x] = std::min(double(d.nbricks[x]), (w - 1.0) / bsz[x] + 1.0);
             int64_t nbx = d.nbricks[x];  // most bricks one atom's window touches along x
             if (w < N[x]) {
                 const int64_t bnd = int64_t(std::ceil((w - 1.0) / bsz[x])) + 2;
@@ -550,6 +555,7 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
             }
             per_atom *= nbx;
         }
+        p->bins.push_back(bin);
         d.brick_off = bricks;
         d.col_off = p->ncols;
         p->ncols += d.nbricks[0] * d.nbricks[1];
@@ -1086,6 +1092,8 @@ hartree_status hartree_atoms_bind(hartree_plan plan, int32_t natoms, const doubl
     SplatArgs a = splat_args(plan, natoms, pos, Z, sigma, atom_offsets);
     hipStream_t s = static_cast<hipStream_t>(stream);
     plan->bound = false;
+    for (int q = 0; q < plan->nprob; ++q) plan->bins[q].atoms = a.atom_off[q + 1] - a.atom_off[q];
+    a.columns = bin_by_columns(plan->nprob, plan->bins.data()) ? 1 : 0;
     hipError_t e = timed(plan, HARTREE_K_BIN, s, [&]() { return run_bin(a, s); });
     if (e != hipSuccess) return hip_fail(e, "atom binning");
     plan->bound = true;

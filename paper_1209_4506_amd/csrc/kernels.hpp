@@ -123,6 +123,7 @@ struct SplatArgs {
     int32_t cap_pa;         // most bricks one atom can touch
     int64_t nbricks_total;
     int32_t ncols;          // columns of bricks along c, all problems
+    int32_t columns;        // 1: binning by columns
     DeviceStatus *status;
     int32_t subtract_background;
     int32_t fp64;

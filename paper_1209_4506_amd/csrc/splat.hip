@@ -10,14 +10,14 @@
 //
 // Binning is deterministic: the per-brick lists are ordered by atom index and
 // every sum below runs in a fixed order, so results do not depend on
-// scheduling.  Two forms, by the largest atom count of a problem (run_bin):
+// scheduling.  Two forms (bin_by_columns says which):
 //
-//   columns (up to kColAtoms atoms per problem)
+//   columns
 //     prep    per atom: wrapped position, weight, window [lo, hi] per axis;
 //             per problem: Q = sum Z (fixed order), for the background Q / Omega
 //     gather  per column of bricks along c: the atoms that touch it, in order,
 //             then each of its bricks' lists from those
-//   visits (more atoms)
+//   visits
 //     count   per atom: the same preparation; +1 on each touched brick
 //     scan    Q; exclusive prefix sum of the brick counts
 //     fill    per atom: write its index into each touched brick's list
@@ -29,6 +29,7 @@
 //   final   per atom: fixed-order sum of its partials over the touched bricks
 #include <algorithm>
 
+#include "bin_rule.hpp"
 #include "splat_common.hpp"
 
 namespace hartree {
@@ -568,7 +569,6 @@ __global__ __launch_bounds__(256) void k_brick_sort(SplatArgs a, int rank_words)
 // Taken over chunks of 4,096 it no longer pays, each column testing all atoms
 // twice: 420 x 420 x 210, 16,384 atoms, 70 us against 69 by visits; 1024^3,
 // 32,768 atoms, 421 against 323.
-constexpr int kColAtoms = 4096;
 constexpr int kColThreads = 256;  // 64, 128 and 512 threads a column are within 15 % of it or slower
 
 // an atom's touched bricks in two words: first brick and number of bricks, 10 bits per axis
@@ -800,8 +800,7 @@ hipError_t run_bin(const SplatArgs &a, hipStream_t s)
     const int64_t nbt = a.nbricks_total;
     int span = 0;
     for (int p = 0; p < a.nprob; ++p) span = std::max(span, a.atom_off[p + 1] - a.atom_off[p]);
-    // every column reads all atoms of its problem and holds its hits in LDS
-    if (span <= kColAtoms) {
+    if (a.columns) {  // (every column holds its hits in LDS: span <= kColAtoms)
         const int atom_blocks = std::max(1, (a.natoms + kPrepThreads - 1) / kPrepThreads);
         const int charge_blocks = a.nprob <= 4 ? a.nprob : (a.nprob + kPrepThreads / 64 - 1) / (kPrepThreads / 64);
         hipLaunchKernelGGL(k_atom_prep, dim3(atom_blocks + charge_blocks), dim3(kPrepThreads), 0, s, a, atom_blocks);
