@@ -365,6 +365,33 @@ void rebuild_launches(hartree_plan p)
     }
 }
 
+// Default tiles of an FP32 batch whose problems can share the launches of an
+// axis: along c the narrowest of their widths (4 or 8 pencils), along a and b the
+// widest tiles where those are the multi-plan launches' own (lengths of 32, 48,
+// 60 and 64 along a, 32 along b).
+void common_tiles(hartree_plan p)
+{
+    for (int x = 0; x < 3; ++x) {
+        const int *list = multi_plans(x);
+        bool whole = true, sized = true;
+        int least = 8;
+        for (int q = 0; q < p->nprob; ++q) {
+            const auto &c = p->cfg[3 * q + x];
+            const AxisPlan &ap = p->desc[q].ax[x];
+            whole = whole && std::find(list, list + kMultiPlans, c.plan) != list + kMultiPlans;
+            sized = sized && 1 << pass_p_log2(p->fp64, ap.n, ap.radix, ap.nstages, 64) == multi_auto_p(ap.n, x);
+            least = std::min(least, c.p_log2);
+        }
+        if (!whole || !(x == 2 ? least >= 2 : sized)) continue;
+        for (int q = 0; q < p->nprob; ++q) {
+            auto &c = p->cfg[3 * q + x];
+            const AxisPlan &ap = p->desc[q].ax[x];
+            c.p_log2 = x == 2 ? least : pass_p_log2(p->fp64, ap.n, ap.radix, ap.nstages, 64);
+            c.pad = 0;
+        }
+    }
+}
+
 hartree_status create(hartree_plan *out, int nprob, const double *cells, const int32_t *dims, int32_t precision,
                       const hartree_plan_opts *opts)
 {
@@ -565,6 +592,7 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
     p->grid_offsets.push_back(grid);
     p->grid_total = grid;
     p->spec_count = spec;
+    if (nprob > 1 && !p->fp64) common_tiles(p);
     rebuild_launches(p);
     p->nbricks = p->splat_ok ? bricks : 0;
     p->capacity = p->splat_ok ? int64_t(p->max_atoms) * cap_per_atom : 0;
