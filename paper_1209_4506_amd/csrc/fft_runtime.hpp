@@ -450,18 +450,24 @@ __global__ __launch_bounds__(256) void k_fft_a_rt(PassArgs a)
     const int mb = int(fdiv(uint32_t(col), d.div_nh));
     const int mc = col - mb * nh;
     Cx<T> *g = reinterpret_cast<Cx<T> *>(a.spec) + d.spec_off + col;
-    const int S = ap.nstages, copy = n * PP, result = S > 0 ? (S - 1) & 1 : 0;
+    // (a single stage leaves most threads idle, one butterfly per pencil: its
+    // result goes to the other copy first, and the multiply is dealt out to all
+    // of them; 16 x 40 x 48 FP32 20 -> 9 us, 8 x 40 x 48 13 -> 8)
+    const int S = ap.nstages, copy = n * PP, result = S > 1 ? (S - 1) & 1 : S;
     auto at = [&](int p, int i) { return i * PP + p; };
     KernelMultiply<T> km{buf + result * copy, PP, p0, &d, mb, mc, energy, T(d.inv_n),
                          ok ? ((mc == 0 || 2 * mc == Nc) ? 1.0 : 2.0) : 0.0, 0.0};
     km.init();
+    auto from_global = [&](int, int i) { return g[int64_t(i) * ncol]; };
     if (S == 0) {
         // length-1 axis: the multiply alone
         if (it.tip == 0) km.store(0, g[0]);
+    } else if (S == 1) {
+        rt_fft<T, WIDE>(it, ap, tw, buf, copy, 0, at, from_global, [&](int p, int i, Cx<T> v) { buf[at(p, i)] = v; });
+        __syncthreads();
+        for (int i = it.tip; i < n; i += it.tpp) km.store(i, buf[at(p0, i)]);
     } else {
-        rt_fft<T, WIDE>(
-            it, ap, tw, buf, copy, 0, at, [&](int, int i) { return g[int64_t(i) * ncol]; },
-            [&](int, int i, Cx<T> v) { km.store(i, v); });
+        rt_fft<T, WIDE>(it, ap, tw, buf, copy, 0, at, from_global, [&](int, int i, Cx<T> v) { km.store(i, v); });
     }
     __syncthreads();
     if (energy) {
