@@ -365,27 +365,39 @@ void rebuild_launches(hartree_plan p)
     }
 }
 
-// Default tiles of an FP32 batch whose problems can share the launches of an
-// axis: along c the narrowest of their widths (4 or 8 pencils), along a and b the
-// widest tiles where those are the multi-plan launches' own (lengths of 32, 48,
-// 60 and 64 along a, 32 along b).
-void common_tiles(hartree_plan p)
+// The tiles of the passes as a plan is created.  In an FP32 batch the problems
+// share the launches of an axis where they can: along c at the narrowest of their
+// widths (4 or 8 pencils), along a and b at the widest tiles where those are the
+// multi-plan launches' own (lengths of 32, 48, 60 and 64 along a, 32 along b).
+void default_tiles(hartree_plan p)
 {
+    p->cfg.resize(3 * size_t(p->nprob));
     for (int x = 0; x < 3; ++x) {
+        std::map<int, TileGrid> of_length;
+        for (const ProbDesc &d : p->desc) {
+            const int64_t nb = d.dims[1], nh = d.dims[3];
+            TileGrid &g = of_length[d.dims[x]];
+            g.batch = p->nprob > 1;
+            g.of.push_back(x == 0   ? TileGrid::Runs{1, nb * nh}
+                           : x == 1 ? TileGrid::Runs{d.dims[0], nh}
+                                    : TileGrid::Runs{1, (d.dims[0] * nb + 1) / 2});
+        }
         const int *list = multi_plans(x);
         bool whole = true, sized = true;
         int least = 8;
         for (int q = 0; q < p->nprob; ++q) {
-            const auto &c = p->cfg[3 * q + x];
             const AxisPlan &ap = p->desc[q].ax[x];
+            auto &c = p->cfg[3 * q + x];
+            c.plan = find_plan(ap.radix, ap.nstages);
+            default_tile(p->fp64, x, ap.n, ap.radix, ap.nstages, of_length[ap.n], c.p_log2, c.pad);
             whole = whole && std::find(list, list + kMultiPlans, c.plan) != list + kMultiPlans;
             sized = sized && 1 << pass_p_log2(p->fp64, ap.n, ap.radix, ap.nstages, 64) == multi_auto_p(ap.n, x);
             least = std::min(least, c.p_log2);
         }
-        if (!whole || !(x == 2 ? least >= 2 : sized)) continue;
+        if (p->nprob == 1 || p->fp64 || !whole || !(x == 2 ? least >= 2 : sized)) continue;
         for (int q = 0; q < p->nprob; ++q) {
-            auto &c = p->cfg[3 * q + x];
             const AxisPlan &ap = p->desc[q].ax[x];
+            auto &c = p->cfg[3 * q + x];
             c.p_log2 = x == 2 ? least : pass_p_log2(p->fp64, ap.n, ap.radix, ap.nstages, 64);
             c.pad = 0;
         }
@@ -535,16 +547,12 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
         for (int k = 0; k < 9; ++k) d.A[k] = A[k];
         d.separable = (ortho && A[0] > 0.0 && A[4] > 0.0 && A[8] > 0.0) ? 1 : 0;
         if (!d.separable) p->general = true;
-        // pass tiles: default radix plan and pencils per workgroup per axis
         for (int x = 0; x < 3; ++x) {
-            int lp, pad;
-            default_tile(p->fp64, x, N[x], d.ax[x].radix, d.ax[x].nstages, lp, pad);
-            if (lp < 0) {
+            if (pass_p_log2(p->fp64, N[x], d.ax[x].radix, d.ax[x].nstages, 64) < 0) {
                 delete p;
                 return fail(HARTREE_ERR_DIMS, "problem %d: length %d needs more threads per pencil than a workgroup has",
                             q, N[x]);
             }
-            p->cfg.push_back({find_plan(d.ax[x].radix, d.ax[x].nstages), lp, pad});
         }
         // tile counts at one pencil per workgroup bound every choice
         const int64_t rows = int64_t(N[0]) * N[1];
@@ -592,7 +600,7 @@ hartree_status create(hartree_plan *out, int nprob, const double *cells, const i
     p->grid_offsets.push_back(grid);
     p->grid_total = grid;
     p->spec_count = spec;
-    if (nprob > 1 && !p->fp64) common_tiles(p);
+    default_tiles(p);
     rebuild_launches(p);
     p->nbricks = p->splat_ok ? bricks : 0;
     p->capacity = p->splat_ok ? int64_t(p->max_atoms) * cap_per_atom : 0;

@@ -158,19 +158,29 @@ void runtime_tile(int fp64, int x, int n, int &p_log2, int &pad)
     }
 }
 
-// Default pencils per tile of the run-time radix passes: as many as leave a
-// CU room for two to four such workgroups, as its kernel's registers allow,
-// and no more than pay.  Measured (us, FP32 unless noted):
+// Default pencils per tile of the run-time radix passes.  Long lengths: as many as
+// leave a CU room for two to four such workgroups, as its kernel's registers
+// allow, and no more than pay.  Measured (us, FP32 unless noted):
 //   a  n = 75: 8 34.8, 16 26.0, 32 22.8; n = 252: 4 82, 8 62, 16 75 (past a third
 //      of the LDS); FP64, two wavefronts per SIMD: n = 135: 8 42, 16 34, 32 39
 //   b  n = 168: 4 15.1, 8 12.6, 16 16.7; n = 625: 2 20.4, 4 18.9, 8 27.5
 //   c  n = 189: 4 16.9, 8 16.4, 16 21.4; n = 280: 2 64, 4 47, 8 57 (past a fourth)
-static int runtime_default_p_log2(int fp64, int x, int n)
+// Along a and b a short length has few butterflies to a pencil, and only wide
+// tiles occupy the 256 threads: up to 256, 2,048 points (3,072 along a in FP64) in
+// at most 64 pencils, and fewer where that leaves less than 256 tiles.  (Not in
+// a batch, whose problems share a launch where their tiles have one width.)
+//   a  n = 16 of 16 x 64 x 2048: 16 34.1, 32 22.4, 64 18.2; of 16 x 40 x 48: 4 to 32 9 to 10, 64 11.5
+//      FP64 n = 4 of 4 x 360 x 360: 16 33.4, 64 12.9; n = 144 of 144 x 360 x 360: 4 284, 16 158
+//   b  n = 16 of 64 x 16 x 2048: 8 43.5, 64 19.0; FP64 n = 9 of 360 x 9 x 360: 8 39.0, 64 19.7
+static int runtime_default_p_log2(int fp64, int x, int n, const TileGrid &g)
 {
     bool twg;
-    int lp = x == 0 ? (fp64 ? 4 : 5) : 3;
+    const bool wide = x < 2 && n <= 256 && !g.batch;
+    int lp = wide ? 6 : (x == 0 ? (fp64 ? 4 : 5) : 3);
     const size_t most = kCuLds / (x == 0 ? (fp64 ? 2 : 3) : (x == 1 || fp64 ? 3 : 4));
-    while (lp > 0 && (runtime_lds(fp64, x, n, lp, 0, twg) > most || twg)) --lp;
+    const int points = x == 0 && fp64 ? 3072 : 2048;
+    while (lp > 0 && (runtime_lds(fp64, x, n, lp, 0, twg) > most || twg || (wide && n << lp > points))) --lp;
+    while (wide && lp > 3 && g.tiles(lp) < 256) --lp;
     return lp;
 }
 
@@ -207,7 +217,7 @@ int find_plan(const int *radix, int nstages)
 // long contiguous segments, a narrow one leaves a CU room for more workgroups
 // and cuts a short grid into more of them; 64 KB and more of LDS for a tile
 // (64 pencils up to n = 150, 32 up to 256, 16 up to 512) leaves two per CU.
-// Measured (us; a forward / with E_H, b forward / inverse, c r2c / c2r):
+// Measured (us; a forward / with E_H, b forward / inverse, c r2c / c2r; n^3):
 //   FP32 a  n = 96: 16 10.8 / 9.4, 64 15.6 / 15.9; 180: 16 18.9 / 18.4, 32 21.8 / 21.3; 192: 8 18.8 / 17.8,
 //           16 23.4 / 18.6, 32 28.7 / 28.2; 360: 8 82 / 79, 16 93 / 91; 256: 8 47.9, 16 34.7, 32 42.2 (rows a
 //           power of two apart share few cache sets: the wide tile's longer segments win, so too at 512)
@@ -221,34 +231,60 @@ int find_plan(const int *radix, int nstages)
 // FP32 tiles of 16 take a pitch pad of one, so that the kernels are the ones
 // of every other width: those with 16 compiled in round some lengths'
 // butterflies in another order and are 0 to 10 % faster.
-void default_tile(int fp64, int x, int n, const int *radix, int nstages, int &p_log2, int &pad)
+// On grids other than cubes (both passes):
+//   short lengths, where plans of two stages leave the threads of a narrow
+//   tile without a butterfly (n = 64: 8 a pencil), once there are tiles enough:
+//     FP32 a  32 x 360 x 360: 16 29.3, 32 20.5, 64 18.2; 64 x 64 x 2048: 16 41.6, 32 30.3, 64 32.6
+//     FP32 b  64 x 32 x 2048: 16 31.9, 64 25.7; 400 x 48 x 20 (400 tiles): 16 13.2, 64 15.4
+//     FP64 a  64 x 100 x 300: 8 26.9, 16 25.1, 32 20.9; 64 x 400 x 20 (138 tiles of 32): 8 14.5, 16 16.5, 32 15.2;
+//             72 x 360 x 360: 8 73.9, 16 64.9, 32 58.9; 160 x 16 x 4096: 8 70.0, 16 61.8; 60 (three stages) of
+//             60 x 192 x 192: 8 22.1, 32 29.4
+//     FP64 b  192 x 32 x 192: 16 19.7, 32 18.7; 400 x 256 x 20: 8 29.3, 16 25.7
+//   long pencils along c in FP64 with less than 256 tiles: 12 x 10 x 200: 4 13.8, 8 16.4; 48 x 40 x 288: 4 15.9, 8 19.4
+void default_tile(int fp64, int x, int n, const int *radix, int nstages, const TileGrid &g, int &p_log2, int &pad)
 {
-    p_log2 = pass_p_log2(fp64, n, radix, nstages, 64);
+    const int widest = pass_p_log2(fp64, n, radix, nstages, 64);
+    p_log2 = widest;
     pad = 0;
-    if (p_log2 < 0) return;
+    if (widest < 0) return;
     if (find_plan(radix, nstages) < 0) {  // (no more pencils than set_config accepts)
-        p_log2 = std::min(p_log2, runtime_default_p_log2(fp64, x, n));
+        p_log2 = std::min(widest, runtime_default_p_log2(fp64, x, n, g));
         return;
     }
     if (x == 2) {
-        const bool eight = fp64 ? n <= 300 : n <= 160 || (n <= 256 && n % 16 == 0);
-        p_log2 = std::min(p_log2, eight ? 3 : 2);
+        const bool eight = fp64 ? n <= 300 && (n < 160 || g.tiles(3) >= 256) : n <= 160 || (n <= 256 && n % 16 == 0);
+        p_log2 = std::min(widest, eight ? 3 : 2);
         return;
     }
     const bool pow2 = (n & (n - 1)) == 0;
     if (fp64) {
-        if (x == 0 && n != 256) {
-            p_log2 = std::min(p_log2, n <= 320 || pow2 ? 3 : 2);
+        const bool two = nstages == 2 && n <= 256;
+        const int wide = x == 0 ? 96 : 48;  // the longest such length that 32 pencils still pay for
+        if (two && n <= wide && widest >= 5 && g.tiles(5) >= 256) {
+            p_log2 = 5;
             return;
         }
-        p_log2 = std::min(p_log2, x == 0 || n <= 160 ? 4 : 3);
+        if (two && (x == 0 || n == 256) && widest >= 4 && g.tiles(4) >= (x == 0 ? 512 : 256)) {
+            p_log2 = 4;
+            return;
+        }
+        if (x == 0 && n != 256) {
+            p_log2 = std::min(widest, n <= 320 || pow2 ? 3 : 2);
+            return;
+        }
+        p_log2 = std::min(widest, x == 0 || n <= 160 ? 4 : 3);
         // (among those no larger in LDS than a pad of one)
         pad = modelled_pad(fp64, n, radix, nstages, p_log2);
         if (pass_tile_lds(fp64, n, p_log2, pad) > pass_tile_lds(fp64, n, p_log2, 1)) pad = 1;
         return;
     }
-    const bool wide = n <= 180 || pow2;
-    p_log2 = std::min(p_log2, wide ? 4 : 3);
+    for (int lp = n <= 48 ? 6 : 5; lp >= 5 && n <= 64; --lp)
+        if (widest >= lp && g.tiles(lp) >= 512) {
+            p_log2 = lp;
+            pad = 1;  // (in a batch no multi-plan tile, which would round otherwise)
+            return;
+        }
+    p_log2 = std::min(widest, n <= 180 || pow2 ? 4 : 3);
     pad = p_log2 == 4 && n < 512 ? 1 : 0;
 }
 

@@ -1,6 +1,8 @@
 // Launch interface between the host library and the kernels.
 #pragma once
 
+#include <vector>
+
 #include "common.hpp"
 
 namespace hartree {
@@ -80,8 +82,23 @@ size_t pass_tile_lds(int fp64, int n, int p_log2, int pad);
 // one does not fit
 size_t runtime_lds(int fp64, int x, int n, int p_log2, int pad, bool &twg);
 void runtime_tile(int fp64, int x, int n, int &p_log2, int &pad);
+// The pencils of a pass along one axis: of each problem with one length on it
+// (they share a launch), `outer` runs of `inner` that tiles do not cross.
+struct TileGrid {
+    struct Runs {
+        int64_t outer, inner;
+    };
+    std::vector<Runs> of;
+    bool batch;  // the plan has several problems
+    int64_t tiles(int p_log2) const
+    {
+        int64_t n = 0;
+        for (const Runs &r : of) n += r.outer * ((r.inner + (int64_t(1) << p_log2) - 1) >> p_log2);
+        return n;
+    }
+};
 // the tile of a pass as plans are created: pencils (log2; negative: none fits) and pitch pad
-void default_tile(int fp64, int x, int n, const int *radix, int nstages, int &p_log2, int &pad);
+void default_tile(int fp64, int x, int n, const int *radix, int nstages, const TileGrid &g, int &p_log2, int &pad);
 int find_plan(const int *radix, int nstages);
 int plan_table_size();
 int plan_table_row(int id, int *radix);  // fills radix[4], returns the stage count

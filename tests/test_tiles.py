@@ -13,6 +13,38 @@ BATCHES = [[(48, 48, 48)] * 3, [(32, 32, 32)] * 2, [(240, 200, 64), (210, 200, 2
            [(72, 150, 60), (240, 180, 72), (150, 60, 120), (90, 90, 240)]]
 
 
+def default_widths(dims, precision):
+    """Pencils per tile along a, b and c of a plan as created (host only)."""
+    import ctypes
+
+    from paper_1209_4506_amd.hartree import LIB
+
+    d, i32 = ctypes.c_double, ctypes.c_int32
+    h, cfg = ctypes.c_void_p(), (i32 * 9)()
+    assert LIB.hartree_plan_create(ctypes.byref(h), (d * 9)(9, 0, 0, 0, 9, 0, 0, 0, 9), (i32 * 3)(*dims), precision, None) == 0
+    assert LIB.hartree_plan_get_config(h, cfg) == 0
+    LIB.hartree_plan_destroy(h)
+    return [1 << cfg[3 * x + 1] for x in range(3)]
+
+
+def test_short_lengths_take_wide_tiles():
+    """Widths that measured faster by an eighth and more than half and a quarter
+    of them, or than twice (short strided lengths, many and few tiles)."""
+    fp64, fp32 = 0, 1
+    for prec, axis, dims, widths in ((fp32, 0, (16, 64, 2048), {64}), (fp32, 1, (64, 16, 2048), {32, 64}),
+                                     (fp32, 1, (16, 16, 4096), {32, 64}), (fp32, 0, (8, 360, 360), {64}),
+                                     (fp64, 0, (4, 360, 360), {64}), (fp64, 0, (16, 16, 4096), {32, 64}),
+                                     (fp64, 0, (144, 360, 360), {16, 32}), (fp64, 1, (360, 9, 360), {32, 64}),
+                                     (fp32, 0, (16, 10, 12), {1, 2, 4, 8, 16, 32}), (fp32, 0, (32, 360, 360), {64}),
+                                     (fp32, 0, (64, 64, 2048), {32, 64}), (fp32, 1, (64, 32, 2048), {32, 64}),
+                                     (fp32, 1, (400, 48, 20), {8, 16}), (fp64, 0, (64, 100, 300), {32}),
+                                     (fp64, 0, (64, 400, 20), {8, 16, 32}), (fp64, 0, (72, 360, 360), {32}),
+                                     (fp64, 0, (160, 16, 4096), {16}), (fp64, 0, (60, 192, 192), {8}),
+                                     (fp64, 0, (96, 192, 192), {8}), (fp64, 2, (12, 10, 200), {1, 2, 4}),
+                                     (fp64, 2, (192, 192, 200), {4, 8})):
+        assert default_widths(dims, prec)[axis] in widths, (prec, axis, dims, default_widths(dims, prec))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dims", BATCHES)
 def test_batches_as_created(dims):
