@@ -688,8 +688,7 @@ __device__ __forceinline__ GenAtom64 gen_atom64(const SplatArgs &a, const ProbDe
         double rb[3];
         g.im = gen_images(in, d, gd, g0, rb);
         g.sc = sqrt(in.inv2s2);
-        // finite, so that the points outside the sphere add zero
-        g.w = fmin(fmax(in.w, -1.7976931348623157e308), 1.7976931348623157e308);
+        g.w = in.w;
     }
     g.run = gen_run(gd.tri[5] * g.sc, qc);
     return g;
@@ -752,7 +751,7 @@ __global__ __launch_bounds__(64 * kWays) void k_splat_general64(SplatArgs a)
                 gen_exps(rn, s, tm, qc, t, in, e);
                 const double w = lane_value(mine.w, q);
 #pragma unroll
-                for (int j = 0; j < kRun; ++j) acc[j] += w * (in[j] ? e[j] : 0.0);
+                for (int j = 0; j < kRun; ++j) acc[j] = in[j] ? fma(w, e[j], acc[j]) : acc[j];
             }
         }
     }

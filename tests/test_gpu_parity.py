@@ -244,6 +244,21 @@ def test_general_cell_images(H, oracle_mod, prec, case):
     assert ef <= (1e-10 if prec == "fp64" else 1e-5)
 
 
+def test_general_cell_infinite_weight(H):
+    """An FP64 width so small that the atom's weight overflows: infinite at the
+    grid point it lies on, and nothing of it anywhere else.  (In FP32 its 1 / (2
+    sigma^2) overflows too, and the point is NaN.)"""
+    say("case infinite weight")
+    plan = H.Plan(CELLS["triclinic"], (20, 18, 36), precision="fp64", max_atoms=2)
+    pos = torch.tensor([[0.0, 0.0, 0.0], [4.0, 3.0, 5.0]], dtype=torch.float64, device="cuda")
+    Z, sig = torch.ones(2, dtype=torch.float64, device="cuda"), torch.tensor([1e-105, 0.8], dtype=torch.float64, device="cuda")
+    both = plan.splat(pos, Z, sig, subtract_background=False)
+    one = plan.splat(pos[1:], Z[1:], sig[1:].contiguous(), subtract_background=False)
+    assert torch.isposinf(both[0, 0, 0])
+    both[0, 0, 0] = one[0, 0, 0]
+    assert torch.equal(both, one)
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_many_atoms_one_problem(H, oracle_mod, prec):
     """33,000 atoms in one problem, more than the binning's bitmap ranks cover
