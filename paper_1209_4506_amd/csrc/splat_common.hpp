@@ -129,6 +129,16 @@ static __constant__ double kExp[17] = {
     1.0 / 0.69314718055994530942, -762123384786.0 / 1099511627776.0, 1.7239444525614835e-13,
     1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0,
     1.0 / 5040.0, 1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0, 0.5, 1.0, 1.0};
+// The exponent as the instruction converts it: saturated, so that 2^n is 0 and
+// infinity for any x (a conversion of the language's is undefined beyond 2^31, from
+// |x| = 1.5e9 on, cutoffs of 5.5e4 sigmas; this costs 0.5 %, a bound on x 1.4 % of the
+// FP64 splat and adjoint).
+__device__ __forceinline__ int exponent64(double n)
+{
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(n));
+    return i;
+}
 __device__ __forceinline__ double exp64(double x)
 {
     const double n = __builtin_rint(x * kExp[0]);
@@ -136,7 +146,7 @@ __device__ __forceinline__ double exp64(double x)
     double e = kExp[3];
 #pragma unroll
     for (int k = 4; k < 17; ++k) e = __builtin_fma(e, r, kExp[k]);
-    return __builtin_ldexp(e, int(n));
+    return __builtin_ldexp(e, exponent64(n));
 }
 // exp(x) and exp(-x): one reduction, and the series' even and odd terms once
 __device__ __forceinline__ void exp64_pair(double x, double &plus, double &minus)
@@ -150,8 +160,8 @@ __device__ __forceinline__ void exp64_pair(double x, double &plus, double &minus
         odd = __builtin_fma(odd, r2, kExp[k]);
         even = __builtin_fma(even, r2, kExp[k + 1]);
     }
-    plus = __builtin_ldexp(__builtin_fma(r, odd, even), int(n));
-    minus = __builtin_ldexp(__builtin_fma(-r, odd, even), -int(n));
+    plus = __builtin_ldexp(__builtin_fma(r, odd, even), exponent64(n));
+    minus = __builtin_ldexp(__builtin_fma(-r, odd, even), exponent64(-n));
 }
 
 }  // namespace hartree

@@ -259,6 +259,24 @@ def test_general_cell_infinite_weight(H):
     assert torch.equal(both, one)
 
 
+def test_cutoff_beyond_every_image(H):
+    """FP64 truncation radii far beyond the last image that counts: exponents
+    down to -1.8e9 give zeros, and the density and the forces are those of 60
+    sigmas, bit for bit."""
+    say("case cutoff beyond every image")
+    dims, L = (16, 15, 12), (30.0, 28.0, 25.0)
+    rng = np.random.default_rng(46)
+    pos, Z, sig = (torch.as_tensor(v, device="cuda") for v in (rng.uniform(0.0, 25.0, (3, 3)), np.array([1.0, 4.0, 6.0]),
+                                                               np.array([0.5, 0.7, 0.9])))
+    g = to_dev(inputs.random_grid(dims, 47), torch.float64)
+    out = []
+    for cutoff in (60.0, 6e4):
+        plan = H.Plan(np.diag(L), dims, precision="fp64", max_atoms=3, cutoff_sigmas=cutoff)
+        out.append((plan.splat(pos, Z, sig), plan.splat_adjoint(pos, Z, sig, g)))
+    assert torch.isfinite(out[1][0]).all() and float(out[1][0].abs().max()) > 0.0
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_many_atoms_one_problem(H, oracle_mod, prec):
     """33,000 atoms in one problem, more than the binning's bitmap ranks cover
