@@ -52,7 +52,7 @@ hipError_t run_a_f32(int plan, int maxn, int grid, hipStream_t s, const PassArgs
     if (plan < 0 || plan >= int(sizeof(kTable) / sizeof(kTable[0])))
         return launch_a_rt<float>(plan == kRuntimeWide, maxn, grid, s, a);
     // the compiled tiles address their pencils with 32-bit lane offsets
-    if (a.pad == 0 && lane_offsets_fit<float>(a)) {
+    if (a.pad == 0 && lane_offsets_fit<float>(a, a.p_log2 == 3 ? threads8<float>(0, maxn) : kPassThreads)) {
         if (a.p_log2 == 2) return kFixed4[plan](grid, lds, s, a);
         if (a.p_log2 == 3) return kFixed8[plan](grid, lds, s, a);
         if (a.p_log2 == 4) return kFixed16[plan](grid, lds, s, a);

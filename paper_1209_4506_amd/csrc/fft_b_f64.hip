@@ -31,7 +31,8 @@ hipError_t run_b_f64(int plan, int maxn, int grid, hipStream_t s, const PassArgs
     if (plan == kMultiPlan) return hipErrorInvalidValue;  // multi-plan launches are FP32 only
     if (plan < 0 || plan >= int(sizeof(kTable) / sizeof(kTable[0])))
         return launch_b_rt<double>(plan == kRuntimeWide, maxn, grid, s, a);
-    if (a.pad == 0 && a.p_log2 == 3 && lane_offsets_fit<double>(a)) return kFixed8[plan](grid, lds, s, a);
+    if (a.pad == 0 && a.p_log2 == 3 && lane_offsets_fit<double>(a, threads8<double>(1, maxn)))
+        return kFixed8[plan](grid, lds, s, a);
     return kTable[plan](grid, lds, s, a);
 }
 }  // namespace hartree

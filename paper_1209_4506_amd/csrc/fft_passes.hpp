@@ -840,12 +840,12 @@ constexpr int threads8(int x, int n)
 
 // Strided tiles of compiled width keep each thread's offset from the tile's
 // first pencil, tip * stride + column, as a 32-bit byte offset: true when that
-// fits for every problem of the launch (the largest stride, tpp - 1 tips; with
-// 512 threads twice the tips, at lengths that leave no such strides).
+// fits for every problem of the launch (the largest stride, the tips of a
+// workgroup of `threads`).
 template <typename T>
-inline bool lane_offsets_fit(const PassArgs &a)
+inline bool lane_offsets_fit(const PassArgs &a, int threads = kPassThreads)
 {
-    const int64_t P = int64_t(1) << a.p_log2, tpp = kPassThreads / P;
+    const int64_t P = int64_t(1) << a.p_log2, tpp = threads / P;
     return ((tpp - 1) * a.col_stride + P) * int64_t(sizeof(Cx<T>)) < (int64_t(1) << 32);
 }
 
