@@ -239,28 +239,14 @@ constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // ------------------------------------------------------------------ access
 // element i of the thread's pencil in the LDS tile
-// An inverse transform runs the forward stages on conjugated data:
-// F^-1 x = conj(F conj x) (unnormalized), so the accessor that feeds the
-// first stage and the one that takes the last stage's output conjugate when
-// cj is set.
 template <typename T>
 struct LdsPencil {
     static constexpr bool kLds = true;
     static constexpr bool kTail = false;
     Cx<T> *buf;
     int pp, p;
-    bool cj;
-    __device__ __forceinline__ Cx<T> load(int i) const
-    {
-        Cx<T> v = buf[i * pp + p];
-        if (cj) v.y = -v.y;
-        return v;
-    }
-    __device__ __forceinline__ void store(int i, Cx<T> v) const
-    {
-        if (cj) v.y = -v.y;
-        buf[i * pp + p] = v;
-    }
+    __device__ __forceinline__ Cx<T> load(int i) const { return buf[i * pp + p]; }
+    __device__ __forceinline__ void store(int i, Cx<T> v) const { buf[i * pp + p] = v; }
     // element u + t, u uniform across the wavefront (see GlobalPencil)
     __device__ __forceinline__ Cx<T> load_at(int u, int t) const { return load(u + t); }
     __device__ __forceinline__ void store_at(int u, int t, Cx<T> v) const { store(u + t, v); }
@@ -274,18 +260,8 @@ struct LdsRow {
     static constexpr bool kTail = false;
     Cx<T> *buf;
     int ldp, p;
-    bool cj;
-    __device__ __forceinline__ Cx<T> load(int i) const
-    {
-        Cx<T> v = buf[p * ldp + i];
-        if (cj) v.y = -v.y;
-        return v;
-    }
-    __device__ __forceinline__ void store(int i, Cx<T> v) const
-    {
-        if (cj) v.y = -v.y;
-        buf[p * ldp + i] = v;
-    }
+    __device__ __forceinline__ Cx<T> load(int i) const { return buf[p * ldp + i]; }
+    __device__ __forceinline__ void store(int i, Cx<T> v) const { buf[p * ldp + i] = v; }
     __device__ __forceinline__ Cx<T> load_at(int u, int t) const { return load(u + t); }
     __device__ __forceinline__ void store_at(int u, int t, Cx<T> v) const { store(u + t, v); }
 };
@@ -474,7 +450,6 @@ __device__ __forceinline__ void fft_static(const Src &src, Dst &dst, const L &ld
     constexpr int Q1 = R1 > 0 ? R1 : 1, Q2 = R2 > 0 ? R2 : 1, Q3 = R3 > 0 ? R3 : 1;
     (void)ap;
     L l = lds;
-    l.cj = false;
     stage_ct<T, R0, stage_maxb<T>(R0), true, Src::kLds, N / R0, 1, 1, INV>(src, l, tw, tip, tpp);
     __syncthreads();
     if constexpr (S == 1) {

@@ -239,7 +239,7 @@ __device__ __forceinline__ void r2c_tile(const PassArgs &a, int prob, int tile)
     const int64_t g_even = d.grid_off + (row0 + (v0 ? 2 * q : 0)) * n;
     const int64_t g_odd = d.grid_off + (row0 + (v1 ? 2 * q + 1 : 0)) * n;
     const T scale = MODE == 0 ? T(0) : T(a.grad_e[prob] * d.dv);
-    const LdsRow<T> lr{buf, ldp, q, false};
+    const LdsRow<T> lr{buf, ldp, q};
     if constexpr (STAGE) {
         // the rows (zero beyond the grid) into the block, every lane on
         // consecutive reals
@@ -268,6 +268,8 @@ __device__ __forceinline__ void r2c_tile(const PassArgs &a, int prob, int tile)
         }
         __syncthreads();
         const LdsRealPairIn<T> in{blk + 2 * q * n, n};
+        // (no compiled plan has a length of 1; without the branches for it the
+        // FP64 kernels of 256 take 80 us for 75 at 192 x 192 x 256)
         if (d.ax[2].nstages > 0) {
             LdsRow<T> out = lr;
             fft_static<T, R0, R1, R2, R3>(in, out, lr, tw, d.ax[2], tip, TPP);
@@ -347,7 +349,7 @@ __device__ __forceinline__ void c2r_tile(const PassArgs &a, int prob, int tile)
     const int tip = tid & (TPP - 1);  // TPP is a power of two
     const bool v0 = 2 * q < rows, v1 = 2 * q + 1 < rows;
     const Cx<T> *spec = reinterpret_cast<const Cx<T> *>(a.spec) + d.spec_off + row0 * nh;
-    const LdsRow<T> lr{buf, ldp, q, false};
+    const LdsRow<T> lr{buf, ldp, q};
     if constexpr (STAGE) {
         Cx<T> *blk = tw + n;
         const int cnt = rows * nh, tot = 2 * P * nh;
@@ -425,7 +427,6 @@ __device__ __forceinline__ void fft_b_tile(const PassArgs &a, int prob, int tile
     extern __shared__ __align__(16) unsigned char smem[];
     const ProbDesc &d = a.desc[prob];
     const int n = d.dims[1], nh = d.dims[3];
-    if (d.ax[1].nstages == 0) return;  // a length-1 axis: identity
     const int tpo = (nh + P - 1) / P;
     const int outer = tile / tpo;
     const int h0 = (tile - outer * tpo) * P;
@@ -438,7 +439,7 @@ __device__ __forceinline__ void fft_b_tile(const PassArgs &a, int prob, int tile
     const int p = tid & (P - 1), tip = CP > 0 ? tid / CP : tid >> a.p_log2;
     Cx<T> *g = reinterpret_cast<Cx<T> *>(a.spec) + d.spec_off + int64_t(outer) * n * nh + h0;
     GlobalPencil<T, (CP > 0)> gp{g, nh, tip * nh + (p < valid ? p : 0), p < valid, a.inv != 0};
-    const LdsPencil<T> lp{buf, PP, p, false};
+    const LdsPencil<T> lp{buf, PP, p};
     fft_static<T, R0, R1, R2, R3>(gp, gp, lp, tw, d.ax[1], tip, TPP);
 }
 
@@ -644,16 +645,14 @@ __device__ __forceinline__ void fft_a_tile(const PassArgs &a, int prob, int tile
     Cx<T> *g = reinterpret_cast<Cx<T> *>(a.spec) + d.spec_off + col0;
     const int lane = tip * ncol + (p < valid ? p : 0);
     GlobalPencil<T, (CP > 0), true> gp{g, ncol, lane, p < valid, false};
-    const LdsPencil<T> lp{buf, PP, p, false};
+    const LdsPencil<T> lp{buf, PP, p};
     KernelMultiply<T> km{buf, PP, p, &d, mb, mc, energy, T(d.inv_n),
                          p < valid ? ((mc == 0 || 2 * mc == Nc) ? 1.0 : 2.0) : 0.0, 0.0};
     km.init();
-    if (d.ax[0].nstages == 0) {
-        // length-1 axis: the multiply alone
-        if (tip == 0) km.store(0, gp.load_at(0, 0));
-    } else {
-        fft_static<T, R0, R1, R2, R3>(gp, km, lp, tw, d.ax[0], tip, TPP);
-    }
+    // (Every compiled plan has stages.  Across these two conditions the compiler
+    // keeps 6 to 11 registers less, four wavefronts per SIMD instead of three:
+    // FP32 60 x 100 x 300 16.5 us a pass, without them 20.8; 180 x 100 x 300 26.3, 32.1)
+    if (d.ax[0].nstages > 0) fft_static<T, R0, R1, R2, R3>(gp, km, lp, tw, d.ax[0], tip, TPP);
     __syncthreads();
     if (energy) {
         const double acc = wave_sum(km.acc);
@@ -667,11 +666,7 @@ __device__ __forceinline__ void fft_a_tile(const PassArgs &a, int prob, int tile
     }
     if (mode == 2) return;
     // inverse along a
-    if (d.ax[0].nstages == 0) {
-        if (tip == 0) gp.store_at(0, 0, lp.load(0));
-    } else {
-        fft_static<T, R0, R1, R2, R3, true>(lp, gp, lp, tw, d.ax[0], tip, TPP);
-    }
+    if (d.ax[0].nstages > 0) fft_static<T, R0, R1, R2, R3, true>(lp, gp, lp, tw, d.ax[0], tip, TPP);
 }
 
 template <typename T, int R0, int R1, int R2, int R3, int CP = 0, int NT = kPassThreads>

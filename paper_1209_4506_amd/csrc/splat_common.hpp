@@ -113,13 +113,6 @@ __device__ __forceinline__ BrickPos brick_pos(const ProbDesc &d, int64_t b)
     return p;
 }
 
-template <typename T>
-__device__ __forceinline__ T expT(T x);
-template <>
-__device__ __forceinline__ float expT<float>(float x) { return expf(x); }
-template <>
-__device__ __forceinline__ double expT<double>(double x) { return exp(x); }
-
 // exp(x): x = n ln 2 + r, |r| <= ln 2 / 2, exp(r) by its Taylor series to
 // r^13 / 13! (the next term is 4e-18).  Without the library's range checks and
 // branches: 2^n underflows to 0 and overflows by itself.  The coefficients are
