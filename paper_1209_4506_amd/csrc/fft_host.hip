@@ -166,8 +166,8 @@ void runtime_tile(int fp64, int x, int n, int &p_log2, int &pad)
 //   b  n = 168: 4 15.1, 8 12.6, 16 16.7; n = 625: 2 20.4, 4 18.9, 8 27.5
 //   c  n = 189: 4 16.9, 8 16.4, 16 21.4; n = 280: 2 64, 4 47, 8 57 (past a fourth)
 // Along a and b a short length has few butterflies to a pencil, and only wide
-// tiles occupy the 256 threads: up to 256, 2,048 points (3,072 along a in FP64) in
-// at most 64 pencils, and fewer where that leaves less than 256 tiles.  (Not in
+// tiles occupy the 256 threads: up to 256, 3,072 points (2,048 along b) in at most
+// 64 pencils, and fewer where that leaves less than 256 tiles.  (Not in
 // a batch, whose problems share a launch where their tiles have one width.)
 //   a  n = 16 of 16 x 64 x 2048: 16 34.1, 32 22.4, 64 18.2; of 16 x 40 x 48: 4 to 32 9 to 10, 64 11.5
 //      FP64 n = 4 of 4 x 360 x 360: 16 33.4, 64 12.9; n = 144 of 144 x 360 x 360: 4 284, 16 158
@@ -178,7 +178,7 @@ static int runtime_default_p_log2(int fp64, int x, int n, const TileGrid &g)
     const bool wide = x < 2 && n <= 256 && !g.batch;
     int lp = wide ? 6 : (x == 0 ? (fp64 ? 4 : 5) : 3);
     const size_t most = kCuLds / (x == 0 ? (fp64 ? 2 : 3) : (x == 1 || fp64 ? 3 : 4));
-    const int points = x == 0 && fp64 ? 3072 : 2048;
+    const int points = x == 0 ? 3072 : 2048;
     while (lp > 0 && (runtime_lds(fp64, x, n, lp, 0, twg) > most || twg || (wide && n << lp > points))) --lp;
     while (wide && lp > 3 && g.tiles(lp) < 256) --lp;
     return lp;
