@@ -167,9 +167,11 @@ void runtime_tile(int fp64, int x, int n, int &p_log2, int &pad)
 //   c  n = 189: 4 16.9, 8 16.4, 16 21.4; n = 280: 2 64, 4 47, 8 57 (past a fourth)
 // Along a and b a short length has few butterflies to a pencil, and only wide
 // tiles occupy the 256 threads: up to 256, 3,072 points (2,048 along b) in at most
-// 64 pencils, and fewer where that leaves less than 256 tiles.  (Not in
-// a batch, whose problems share a launch where their tiles have one width.)
-//   a  n = 16 of 16 x 64 x 2048: 16 34.1, 32 22.4, 64 18.2; of 16 x 40 x 48: 4 to 32 9 to 10, 64 11.5
+// 64 pencils, and fewer where that leaves less than 384 tiles (256 along a in
+// FP64) or half of each empty.  (Not in a batch, whose problems share a launch
+// where their tiles have one width.)
+//   a  n = 16 of 16 x 64 x 2048: 16 34.1, 32 22.4, 64 18.2; of 16 x 40 x 48: 4 to 32 9 to 10, 64 11.5;
+//      n = 35 of 35 x 192 x 192 (291 tiles of 64, 582 of 32): 32 14.4, 64 18.7
 //      FP64 n = 4 of 4 x 360 x 360: 16 33.4, 64 12.9; n = 144 of 144 x 360 x 360: 4 284, 16 158
 //   b  n = 16 of 64 x 16 x 2048: 8 43.5, 64 19.0; FP64 n = 9 of 360 x 9 x 360: 8 39.0, 64 19.7
 static int runtime_default_p_log2(int fp64, int x, int n, const TileGrid &g)
@@ -180,7 +182,8 @@ static int runtime_default_p_log2(int fp64, int x, int n, const TileGrid &g)
     const size_t most = kCuLds / (x == 0 ? (fp64 ? 2 : 3) : (x == 1 || fp64 ? 3 : 4));
     const int points = x == 0 ? 3072 : 2048;
     while (lp > 0 && (runtime_lds(fp64, x, n, lp, 0, twg) > most || twg || (wide && n << lp > points))) --lp;
-    while (wide && lp > 3 && g.tiles(lp) < 256) --lp;
+    const int least = x == 0 && fp64 ? 256 : 384;
+    while (wide && lp > 3 && !g.enough(lp, least)) --lp;
     return lp;
 }
 
@@ -260,11 +263,11 @@ void default_tile(int fp64, int x, int n, const int *radix, int nstages, const T
     if (fp64) {
         const bool two = nstages == 2 && n <= 256;
         const int wide = x == 0 ? 96 : 48;  // the longest such length that 32 pencils still pay for
-        if (two && n <= wide && widest >= 5 && g.tiles(5) >= 256) {
+        if (two && n <= wide && widest >= 5 && g.enough(5, 256)) {
             p_log2 = 5;
             return;
         }
-        if (two && (x == 0 || n == 256) && widest >= 4 && g.tiles(4) >= (x == 0 ? 512 : 256)) {
+        if (two && (x == 0 || n == 256) && widest >= 4 && g.enough(4, x == 0 ? 512 : 256)) {
             p_log2 = 4;
             return;
         }
@@ -279,7 +282,7 @@ void default_tile(int fp64, int x, int n, const int *radix, int nstages, const T
         return;
     }
     for (int lp = n <= 48 ? 6 : 5; lp >= 5 && n <= 64; --lp)
-        if (widest >= lp && g.tiles(lp) >= 512) {
+        if (widest >= lp && g.enough(lp, 512)) {
             p_log2 = lp;
             pad = 1;  // (in a batch no multi-plan tile, which would round otherwise)
             return;

@@ -96,6 +96,13 @@ struct TileGrid {
         for (const Runs &r : of) n += r.outer * ((r.inner + (int64_t(1) << p_log2) - 1) >> p_log2);
         return n;
     }
+    // at least `least` tiles of a width that some run more than half fills
+    bool enough(int p_log2, int64_t least) const
+    {
+        int64_t most = 0;
+        for (const Runs &r : of) most = r.inner > most ? r.inner : most;
+        return tiles(p_log2) >= least && (most << 1) > (int64_t(1) << p_log2);
+    }
 };
 // the tile of a pass as plans are created: pencils (log2; negative: none fits) and pitch pad
 void default_tile(int fp64, int x, int n, const int *radix, int nstages, const TileGrid &g, int &p_log2, int &pad);
