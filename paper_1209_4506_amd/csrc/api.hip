@@ -223,7 +223,7 @@ struct hartree_plan_s {
     // side streams of a batched plan: the launch groups of one pass (problems
     // with different pass shapes) write disjoint problems, so they run side by
     // side, forked from and joined back into the caller's stream by events
-    // (under capture: parallel branches of the graph).  Default priority.
+    // (under capture: in order on the caller's stream).  Default priority.
     static constexpr int kSide = 3;
     hipStream_t side[kSide] = {};
     hipEvent_t fork_ev = nullptr;

@@ -236,7 +236,8 @@ int find_plan(const int *radix, int nstages)
 // butterflies in another order and are 0 to 10 % faster.
 // On grids other than cubes (both passes):
 //   short lengths, where plans of two stages leave the threads of a narrow
-//   tile without a butterfly (n = 64: 8 a pencil), once there are tiles enough:
+//   tile without a butterfly (n = 64: 8 a pencil), once there are tiles enough
+//   of a width that some run more than half fills:
 //     FP32 a  32 x 360 x 360: 16 29.3, 32 20.5, 64 18.2; 64 x 64 x 2048: 16 41.6, 32 30.3, 64 32.6
 //     FP32 b  64 x 32 x 2048: 16 31.9, 64 25.7; 400 x 48 x 20 (400 tiles): 16 13.2, 64 15.4
 //     FP64 a  64 x 100 x 300: 8 26.9, 16 25.1, 32 20.9; 64 x 400 x 20 (138 tiles of 32): 8 14.5, 16 16.5, 32 15.2;

@@ -882,7 +882,11 @@ hipError_t run_adjoint_general(const SplatArgs &a, hipStream_t s)
     const int nb = int(a.nbricks_total);
     int split = nb < kFewBricks ? 8 : 2;
     if (a.fp64) {
-        // (72 x 80 x 90, 270 bricks of 8 x 8 x 32: 1 105 us, 2 79, 4 74, 6 72, 8 76)
+        // More shares fill the chip and repeat a brick's culling.  us with the
+        // binning, 1 / 2 / 4 / 8 shares, bricks of 8 x 8 x 32 and atoms as given:
+        // 72 and 88: 221 / 136 / 89 / 74    300 and 409: 328 / 218 / 193 / 187
+        // 784 and 1,123: 614 / 498 / 465 / 472    1,024 and 335: 167 / 160 / 170 / 200
+        // 2,000 and 655: 279 / 276 / 302 / 365    7,200 and 11,059: 3,674 / 3,744 / 3,802 / 4,014
         if (nb >= kFewBricks && nb < 4 * kFewBricks) split = 4;
         hipLaunchKernelGGL(k_adjoint_general64, dim3(nb * split), dim3(64 * kWays), 0, s, a, split);
     } else {

@@ -212,6 +212,7 @@ def test_solve_backward_concurrent_chains(H, prec, kind):
         assert_same(step.outputs(), ref, "solve_backward replay %d" % rep)
 
 
+# (hartree_solve_backward records the chains of such plans in order too)
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_captured_groups_in_order(H, prec):
     """A batched plan whose passes have several launch groups: under capture

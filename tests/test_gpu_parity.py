@@ -466,6 +466,8 @@ def test_binding_pairs(H, prec, case):
     assert got == want
 
 
+# (compared with each other here, at the bounds that the parity tests have
+# against the oracle; test_long_columns compares both with the oracle)
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 @pytest.mark.parametrize("natoms", [1, 255, 1025, 4095, 4096])
 @pytest.mark.parametrize("case", ["diagonal", "skew", "batched"])
