@@ -244,6 +244,44 @@ def test_general_cell_images(H, oracle_mod, prec, case):
     assert ef <= (1e-10 if prec == "fp64" else 1e-5)
 
 
+def test_general_cell_rounding(H):
+    """FP64 density and forces in a sheared cell against extended precision.
+    Wrapping an atom's position into the cell rounds it four times or so, by
+    2.6e-16 each (root mean square of coordinates of 4 to 8): 5e-16 a component,
+    and 0.85e-15 of the density's norm (norm of a Gaussian's gradient over its
+    own: 1 / (sqrt(2) sigma), three components, sigma 0.75), 1.5 times that of the
+    forces'.  Everything after the wrapping has to stay below that."""
+    LD = np.longdouble
+    dims, natoms = (40, 36, 50), 20
+    rng = np.random.default_rng(2)
+    L = np.array(dims) * 0.2
+    cell = np.array([[L[0], 0, 0], [0.25 * L[1], L[1], 0], [-0.15 * L[2], 0.2 * L[2], L[2]]])
+    pos, Z, sig = rng.uniform(0, 1, (natoms, 3)) @ cell, rng.uniform(1, 6, natoms), rng.uniform(0.6, 0.9, natoms)
+    g = rng.standard_normal(dims)
+    plan = H.Plan(cell, dims, precision="fp64", max_atoms=natoms)
+    R, q, w = (to_dev(x, torch.float64) for x in (pos, Z, sig))
+    rho = plan.splat(R, q, w, subtract_background=False).cpu().numpy()
+    f = plan.splat_adjoint(R, q, w, to_dev(g, torch.float64)).cpu().numpy()
+    ref, want = np.zeros(rho.size, LD), np.zeros((natoms, 3), LD)
+    inv = np.linalg.inv(cell)
+    for a in range(natoms):
+        mid, half = pos[a] @ inv * dims, 9.0 * sig[a] * np.linalg.norm(inv, axis=0) * dims
+        ix = [np.arange(int(m - h) - 1, int(m + h) + 2) for m, h in zip(mid, half)]
+        grid = np.meshgrid(*[i.astype(LD) for i in ix], indexing="ij")
+        d = sum(i[..., None] * (row.astype(LD) / n) for i, row, n in zip(grid, cell, dims)) - pos[a].astype(LD)
+        s = LD(sig[a])
+        r2 = (d * d).sum(-1)
+        e = np.where(r2 <= 81 * s * s, LD(Z[a]) / (s * np.sqrt(2 * np.arccos(LD(-1)))) ** 3 * np.exp(-r2 / (2 * s * s)), 0)
+        flat = np.ravel_multi_index(np.meshgrid(*ix, indexing="ij"), dims, mode="wrap")
+        np.add.at(ref, flat.ravel(), e.ravel())
+        want[a] = ((e * g.reshape(-1)[flat])[..., None] * d).sum((0, 1, 2)) / (s * s)
+    er = np.linalg.norm((rho.reshape(-1) - ref).astype(float)) / np.linalg.norm(ref.astype(float))
+    ef = np.linalg.norm((f - want).astype(float)) / np.linalg.norm(want.astype(float))
+    say("  rho rel %.3e  force rel %.3e" % (er, ef))
+    assert er <= 0.85e-15
+    assert ef <= 1.28e-15
+
+
 def test_general_cell_infinite_weight(H):
     """An FP64 width so small that the atom's weight overflows: infinite at the
     grid point it lies on, and nothing of it anywhere else.  (In FP32 its 1 / (2
