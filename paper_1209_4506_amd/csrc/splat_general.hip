@@ -17,8 +17,8 @@
 //
 // Bound by vector and exponential issue over the points near the spheres.
 // Diamond FCC cell, 160^3, 1,024 atoms, FP32: splat 896 -> 134 us, adjoint
-// 1,492 -> 163 us; sheared cell, 72 x 80 x 90, 108 atoms, FP64: 450 -> 48 and
-// 624 -> 73 us (before: every point of every listed brick, with the wrapped
+// 1,492 -> 163 us; sheared cell, 72 x 80 x 90, 108 atoms, FP64: 450 -> 50 and
+// 624 -> 75 us (before: every point of every listed brick, with the wrapped
 // index arithmetic per pair, and one pass over LDS per atom).
 #include "splat_common.hpp"
 
