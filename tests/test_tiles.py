@@ -41,7 +41,8 @@ def test_short_lengths_take_wide_tiles():
                                      (fp64, 0, (64, 400, 20), {8, 16, 32}), (fp64, 0, (72, 360, 360), {32}),
                                      (fp64, 0, (160, 16, 4096), {16}), (fp64, 0, (60, 192, 192), {8}),
                                      (fp64, 0, (96, 192, 192), {8}), (fp64, 2, (12, 10, 200), {1, 2, 4}),
-                                     (fp64, 2, (192, 192, 200), {4, 8})):
+                                     (fp64, 2, (192, 192, 200), {4, 8}), (fp32, 0, (135, 168, 189), {16}),
+                                     (fp32, 0, (35, 192, 192), {16, 32}), (fp32, 1, (2000, 24, 20), {8, 16})):
         assert default_widths(dims, prec)[axis] in widths, (prec, axis, dims, default_widths(dims, prec))
 
 
